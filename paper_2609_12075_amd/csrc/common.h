@@ -56,14 +56,16 @@ __device__ __forceinline__ void xcd_remap(int& bx, int& by, int& bz) {
 // shares, instead of every M tile of a few columns (which would stream all
 // of A through the L2 again for every few columns).
 __device__ __forceinline__ void xcd_remap_grouped(int& bx, int& by, int& bz, int GM) {
-  const long gx = gridDim.x, gy = gridDim.y, T = gx * gy * (long)gridDim.z;
-  const long L = blockIdx.x + gx * (blockIdx.y + gy * (long)blockIdx.z);
-  const long q = T / 8, r = T % 8, x = L % 8, j = L / 8;
-  const long u = x * q + (x < r ? x : r) + j;
-  const long plane = gx * gy, v = u % plane;
+  // 32-bit: a grid of 2^32 blocks, each with an output of its own, would not
+  // fit the card's memory (the 64-bit divisions cost every launch ~0.1 us)
+  const unsigned gx = gridDim.x, gy = gridDim.y, T = gx * gy * gridDim.z;
+  const unsigned L = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+  const unsigned q = T / 8, r = T % 8, x = L % 8, j = L / 8;
+  const unsigned u = x * q + (x < r ? x : r) + j;
+  const unsigned plane = gx * gy, v = u % plane;
   bz = (int)(u / plane);
-  const long g = v / (GM * gy), m0 = g * GM, gm = gx - m0 < GM ? gx - m0 : GM;
-  const long local = v - g * GM * gy;
+  const unsigned g = v / (GM * gy), m0 = g * GM, gm = gx - m0 < (unsigned)GM ? gx - m0 : GM;
+  const unsigned local = v - g * GM * gy;
   bx = (int)(m0 + local % gm);
   by = (int)(local / gm);
 }
