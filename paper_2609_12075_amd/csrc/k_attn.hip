@@ -322,64 +322,114 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnArgs a) {
       bf16x4{(bf16)(acc[0] * inv), (bf16)(acc[1] * inv), (bf16)(acc[2] * inv), (bf16)(acc[3] * inv)};
 }
 
-// fp32 attention: one wave per (query, head, request); keys in chunks of 64
-// (one per lane), online softmax; each lane accumulates hd/64 output dims.
-__global__ void __launch_bounds__(64) attn_f32_kernel(AttnArgs a) {
-  __shared__ float p[64];
-  const int lane = threadIdx.x;
-  const int qi = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int g = h / (a.Hq / a.Hkv);
-  const int hd = a.hd;
-  const float* q = reinterpret_cast<const float*>(a.q) + (long)b * a.q_sb + (long)h * a.q_sh + (long)qi * a.q_si;
-  constexpr int MAXD = 4;   // hd <= 256
-  float acc[MAXD] = {0.f, 0.f, 0.f, 0.f};
+// fp32 attention: the same row decomposition (query head within its KV group,
+// query position) in tiles of 16 rows, both products on the fp32 matrix
+// instructions, operands straight from global memory into registers. A
+// block's NW waves split the keys (16 keys at a time, tile t to wave t % NW)
+// and merge their (max, sum, output) through LDS in wave order. The score
+// tile is computed transposed (S^T = K Q^T), so a lane holds four keys of one
+// query, and those are the P operand of the second product as they are. What
+// bounds it is latency: a wave of the small model's attention (90-180 keys)
+// has one or two key tiles, whose loads are all issued before the first use.
+template <int HDP>
+__global__ void __launch_bounds__(512) attn_f32_kernel(AttnArgs a) {
+  constexpr int NW = 8, NC = HDP / 16;               // 16-wide chunks of the head dimension
+  constexpr int REC = HDP / 4 + 4;                   // merge record of a lane: output, max, sum, pad
+  __shared__ __attribute__((aligned(16))) float mg[NW / 2][64 * REC];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int g = blockIdx.y, b = blockIdx.z, G = a.Hq / a.Hkv, hd = a.hd;
+  const int r = blockIdx.x * 16 + lr;
+  const bool rvalid = r < G * a.Lq;
+  const int jh = rvalid ? r / a.Lq : 0, qi = rvalid ? r % a.Lq : 0, h = g * G + jh;
+  const float* qp = reinterpret_cast<const float*>(a.q) + (long)b * a.q_sb + (long)h * a.q_sh + (long)qi * a.q_si;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 qf[NC], o[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int d = c * 16 + lk * 4;
+    qf[c] = d < hd ? *reinterpret_cast<const f32x4*>(qp + d) : zero;
+    o[c] = zero;
+  }
+  const int len0 = a.seg[0].len, total = len0 + a.seg[1].len, nt = (total + 15) / 16;
   float m_run = -INFINITY, l_run = 0.f;
-  const int len0 = a.seg[0].len, total = len0 + a.seg[1].len;
-  for (int k0 = 0; k0 < total; k0 += 64) {
-    const int kg = k0 + lane;
-    float sc = -INFINITY;
-    if (kg < total) {
-      const int which = kg < len0 ? 0 : 1, key = which ? kg - len0 : kg;
-      const AttnSeg& s = a.seg[which];
-      const float* kp = reinterpret_cast<const float*>(s.k) + (long)b * s.k_sb + (long)g * s.k_sh + (long)key * s.k_si;
-      float dot = 0.f;
-      for (int d = 0; d < hd; ++d) dot = fmaf(q[d], kp[d], dot);
-      sc = dot * a.scale;
+  auto row = [&](int key, bool is_v) -> const float* {
+    const int which = key < len0 ? 0 : 1, kk = which ? key - len0 : key;
+    const AttnSeg& s = a.seg[which];
+    return is_v ? reinterpret_cast<const float*>(s.v) + (long)b * s.v_sb + (long)g * s.v_sh + (long)kk * s.v_si
+                : reinterpret_cast<const float*>(s.k) + (long)b * s.k_sb + (long)g * s.k_sh + (long)kk * s.k_si;
+  };
+  for (int t = wave; t < nt; t += NW) {
+    // keys past the end read the last key's rows; their scores become -inf
+    const float* kp = row(min(t * 16 + lr, total - 1), false);
+    f32x4 kf[NC], vf[NC];                            // vf[c][e]: V[key 4 lk + e][16 c + lr]
+#pragma unroll
+    for (int c = 0; c < NC; ++c) kf[c] = c * 16 + lk * 4 < hd ? *reinterpret_cast<const f32x4*>(kp + c * 16 + lk * 4) : zero;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float* vp = row(min(t * 16 + lk * 4 + e, total - 1), true);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) vf[c][e] = c * 16 + lr < hd ? vp[c * 16 + lr] : 0.f;
     }
-    float mx = sc;
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    const float m_new = fmaxf(m_run, mx);
-    const float pe = kg < total ? __expf(sc - m_new) : 0.f;
-    float ps = pe;
-    for (int o = 32; o > 0; o >>= 1) ps += __shfl_xor(ps, o);
-    const float alpha = __expf(m_run - m_new);
+    f32x4 sc = zero;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[c][e], sc, 0, 0, 0);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sc[e] = t * 16 + lk * 4 + e < total ? sc[e] * a.scale : -INFINITY;
+      mx = fmaxf(mx, sc[e]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m_run, mx), alpha = __expf(m_run - m_new);
+    float ps = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sc[e] = __expf(sc[e] - m_new);
+      ps += sc[e];
+    }
+    ps += __shfl_xor(ps, 16);
+    ps += __shfl_xor(ps, 32);
     l_run = l_run * alpha + ps;
     m_run = m_new;
-    p[lane] = pe;
-    __syncthreads();
-    for (int j = 0; j < MAXD; ++j) acc[j] *= alpha;
-    const int nk = min(64, total - k0);
-    for (int kk = 0; kk < nk; ++kk) {
-      const int kg2 = k0 + kk;
-      const int which = kg2 < len0 ? 0 : 1, key = which ? kg2 - len0 : kg2;
-      const AttnSeg& s = a.seg[which];
-      const float* vp = reinterpret_cast<const float*>(s.v) + (long)b * s.v_sb + (long)g * s.v_sh + (long)key * s.v_si;
-      const float pk = p[kk];
 #pragma unroll
-      for (int j = 0; j < MAXD; ++j) {
-        const int d = lane + 64 * j;
-        if (d < hd) acc[j] = fmaf(pk, vp[d], acc[j]);
-      }
+    for (int c = 0; c < NC; ++c) {
+      o[c] *= alpha;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][e], sc[e], o[c], 0, 0, 0);
+    }
+  }
+  // merge the waves, the upper half into the lower until wave 0 holds all (a
+  // wave without keys has max -inf and sum 0, and weighs nothing)
+  for (int n = NW / 2; n > 0; n /= 2) {
+    if (wave >= n && wave < 2 * n) {
+      float* dst = mg[wave - n] + lane * REC;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) *reinterpret_cast<f32x4*>(dst + 4 * c) = o[c];
+      dst[HDP / 4] = m_run;
+      dst[HDP / 4 + 1] = l_run;
+    }
+    __syncthreads();
+    if (wave < n) {
+      const float* src = mg[wave] + lane * REC;
+      const float m2 = src[HDP / 4], l2 = src[HDP / 4 + 1], m = fmaxf(m_run, m2);
+      const float w1 = m_run == m ? 1.f : __expf(m_run - m), w2 = m2 == m ? 1.f : __expf(m2 - m);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) o[c] = o[c] * w1 + *reinterpret_cast<const f32x4*>(src + 4 * c) * w2;
+      l_run = l_run * w1 + l2 * w2;
+      m_run = m;
     }
     __syncthreads();
   }
+  if (wave != 0 || !rvalid) return;
   float* op = reinterpret_cast<float*>(a.o) + (long)b * a.o_sb + (long)h * a.o_sh + (long)qi * a.o_si;
   const float inv = 1.0f / l_run;
 #pragma unroll
-  for (int j = 0; j < MAXD; ++j) {
-    const int d = lane + 64 * j;
-    if (d < hd) op[d] = acc[j] * inv;
-  }
+  for (int c = 0; c < NC; ++c)
+    if (c * 16 + lk * 4 < hd) *reinterpret_cast<f32x4*>(op + c * 16 + lk * 4) = o[c] * inv;
 }
 
 
@@ -759,7 +809,10 @@ static void attn_plan(const AttnArgs& a, int& splits, int& kchunk, int& ks) {
 void launch_attention(const AttnArgs& a, hipStream_t s) {
   if (a.B <= 0 || a.Lq <= 0) return;
   if (a.et == ET_F32) {
-    hipLaunchKernelGGL(attn_f32_kernel, dim3(a.Lq, a.Hq, a.B), dim3(64), 0, s, a);
+    const dim3 grid(((a.Hq / a.Hkv) * a.Lq + 15) / 16, a.Hkv, a.B);
+    if (a.hd <= 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(512), 0, s, a);
+    else if (a.hd <= 128) hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL(attn_f32_kernel<256>, grid, dim3(512), 0, s, a);
     return;
   }
   // the direct-load kernel keeps scores in log2 units scaled by a positive
