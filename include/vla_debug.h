@@ -160,9 +160,11 @@ vla_status vla_debug_sync_probe(int kind, int grid, int iters, int words, int sp
  *  rms != 0: the RMSNorm of the input rows folded in (not with mode 1);
  *  norm_follows != 0: a row norm of the output follows (residual projections).
  *  plan: int[8] = weight rows and activation rows per tile, number of K
- *  ranges, K length per range, kernel kind (0 register-pipelined, 1
- *  LDS-staged, 2 small-M, 3 large-tile, 4 LDS-staged with K-steps of 128),
- *  LDS stages, K-step length, wave groups sharing each K-step.
+ *  ranges, K length per range, kernel kind (0 register-pipelined, or,
+ *  where the last number is over 1, the waves of a block split K; 1
+ *  LDS-staged; 2 the waves split K, few rows or a folded norm; 3 large-tile;
+ *  4 LDS-staged with K-steps of 128), LDS stages, K-step length, wave groups
+ *  sharing each K-step (kinds 1-4) or waves among which K is split.
  * Status 1 (VLA_EINVAL) on bad arguments.
  */
 vla_status vla_debug_gemm_plan(int M, int N, int K, int mode, int out_bf16, int rms, int norm_follows, int* plan);
@@ -180,9 +182,9 @@ vla_status vla_debug_gemm_plan(int M, int N, int K, int mode, int out_bf16, int 
  * plan (may be NULL): int[9] set to
  * the kernel's tile (weight rows, activation rows), number of K ranges
  * (1 = one kernel, > 1 = partial + reduce kernels), epilogue mode, kernel
- * kind (0 register-pipelined, 1 LDS-staged, 2 small-M, 3 large-tile,
- * 4 LDS-staged with K-steps of 128), LDS stages, K-step length, the
- * number of 4-wave groups that share each K-step, and 1 when the
+ * kind (as vla_debug_gemm_plan gives it), LDS stages, K-step length, the
+ * number of 4-wave groups that share each K-step or of waves that split K,
+ * and 1 when the
  * projection normalises its input rows (folded RMSNorm), else 0.
  */
 vla_status vla_debug_replay_gemm(vla_model m, int which, int batch, int iters, hipStream_t stream, double* flops,

@@ -246,128 +246,6 @@ __global__ void __launch_bounds__(256) splitk_reduce_norm_kernel(GemmArgs a, Nor
   rownorm::store_row<NVW, WPR>(n, r, rok, v, wv, w, lane, g, b, red);
 }
 
-// ---------------------------------------------------------------- small-M kernel
-// For products with few activation rows (the action stage at small batch),
-// where a tile's work is a short K loop and the cost is the memory round
-// trip rather than the matrix work. A block owns 16 * TN weight rows and 64
-// activation rows; its four waves take interleaved 32-wide K chunks (wave w:
-// chunks w, w + 4, ...) and each wave issues the loads of CPW chunks before
-// its first matrix instruction, so one round trip covers 4 * CPW * 32 of K.
-// Loads are unconditional from clamped addresses (out-of-range fragments are
-// zeroed after the load), which keeps them all in flight together. The wave
-// partials are summed in LDS in wave order and the epilogue runs once per
-// output (no atomics: results do not depend on timing).
-template <int TN, int MODE, int RMS = 0>
-__global__ void __launch_bounds__(256) gemm_skinny_kernel(GemmArgs a) {
-  constexpr int BM = 64, BN = 16 * TN, CPW = 8;
-  __shared__ __attribute__((aligned(16))) float red[4][BM][BN];
-  __shared__ float rsq[RMS ? 4 : 1][RMS ? BM : 1], rsc[RMS ? BM : 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int bx, by, bz;
-  xcd_remap_grouped(bx, by, bz, 8);
-  const int m0 = bx * BM, n0 = by * BN;
-  (void)bz;
-  const int kbeg = 0, kend = a.K;
-  const bf16* W = reinterpret_cast<const bf16*>(a.W);
-  const bf16* A = reinterpret_cast<const bf16*>(a.A);
-  const int lr = lane & 15, lk = (lane >> 4) * 8;
-  // this lane's fragment rows (clamped into the operands) and their validity
-  const bf16* wrow[TN];
-  bool wok[TN];
-#pragma unroll
-  for (int i = 0; i < TN; ++i) {
-    const int n = n0 + i * 16 + lr;
-    wok[i] = n < a.N;
-    wrow[i] = W + (long)min(n, a.N - 1) * a.ldw;
-  }
-  const bf16* arow[4];
-  bool aok[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int m = m0 + j * 16 + lr;
-    aok[j] = m < a.M;
-    arow[j] = A + (long)min(m, a.M - 1) * a.lda;
-  }
-  f32x4 acc[TN][4];
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float rs[4] = {0.f, 0.f, 0.f, 0.f}, rs2[4] = {0.f, 0.f, 0.f, 0.f};   // RMS: sums of squares of this lane's A fragments
-
-  for (int k0 = kbeg + wave * 32; k0 < kend; k0 += 4 * 32 * CPW) {
-    bf16x8 wf[CPW][TN], af[CPW][4];
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) {
-      const int k = k0 + c * 128 + lk;
-      const int kc = min(k, a.K - 8);
-#pragma unroll
-      for (int i = 0; i < TN; ++i) wf[c][i] = *reinterpret_cast<const bf16x8*>(wrow[i] + kc);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) af[c][j] = *reinterpret_cast<const bf16x8*>(arow[j] + kc);
-    }
-    // keep every load of the round ahead of the matrix work
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int c = 0; c < CPW; ++c) {
-      const bool kok = k0 + c * 128 + lk < kend;
-#pragma unroll
-      for (int i = 0; i < TN; ++i)
-        if (!(kok && wok[i])) wf[c][i] = bf16x8{};
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (!(kok && aok[j])) af[c][j] = bf16x8{};
-      if constexpr (RMS) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sumsq8(af[c][j], rs[j], rs2[j]);
-      }
-#pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[c][i], af[c][j], acc[i][j], 0, 0, 0);
-    }
-  }
-  // lane holds rows n = 16 i + 4 (lane >> 4) + e, column m = 16 j + (lane & 15)
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      *reinterpret_cast<f32x4*>(&red[wave][j * 16 + lr][i * 16 + (lane >> 4) * 4]) = acc[i][j];
-  if constexpr (RMS) {
-    // every A element of the block's rows was read by exactly one lane: add
-    // the four K-chunk lanes of a row, then the waves, in wave order
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      rs[j] += rs2[j];
-      rs[j] += __shfl_xor(rs[j], 16);
-      rs[j] += __shfl_xor(rs[j], 32);
-    }
-    if (lane < 16) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rsq[wave][j * 16 + lr] = rs[j];
-    }
-  }
-  __syncthreads();
-  if constexpr (RMS) {
-    if (tid < BM) rsc[tid] = rsqrtf((rsq[0][tid] + rsq[1][tid] + rsq[2][tid] + rsq[3][tid]) / (float)a.rms_in + a.rms_eps);
-    __syncthreads();
-  }
-  if (a.epi_vec) {
-    tile_epilogue<MODE, BN, BM, 256, BN, 4>(a, &red[0][0][0], m0, n0, tid, RMS ? rsc : nullptr);
-    return;
-  }
-#pragma unroll
-  for (int c = tid; c < BM * BN / 4; c += 256) {
-    const int mr = c / (BN / 4), nc = (c % (BN / 4)) * 4;
-    f32x4 t = *reinterpret_cast<const f32x4*>(&red[0][mr][nc]) + *reinterpret_cast<const f32x4*>(&red[1][mr][nc]) +
-              *reinterpret_cast<const f32x4*>(&red[2][mr][nc]) + *reinterpret_cast<const f32x4*>(&red[3][mr][nc]);
-    if constexpr (RMS) t = row_scale(t, rsc[mr]);
-    float v[4] = {t[0], t[1], t[2], t[3]};
-    epilogue4<MODE>(a, m0 + mr, n0 + nc, v);
-  }
-}
-
 // ---------------------------------------------------------------- multi-stage kernel
 // For products with many activation rows (the VLM stage; the action stage at
 // larger batches). Operand tiles move global -> LDS with the CDNA4 direct
@@ -822,17 +700,13 @@ static GemmPlan plan_base(const GemmArgs& a) {
     p.splits = std::max(1, (nk + ksteps - 1) / ksteps);
   };
   if (a.a_type == ET_BF16 && a.zeros) {
-    // few activation rows and many weight rows: the small-M kernel (one
-    // memory round trip per 1024 of K, no K split); also for 1024-1535
-    // weight rows when K fits one round trip, instead of K ranges and their
-    // reduce (the DiT head's output and cross-attention projections at batch
-    // 1-3: a DiT step at batch 1 1.110 -> 1.054 ms; narrower products such as
-    // the SmolVLA-shaped O projection, 720 x 960, measured slower this way)
-    if (a.M <= 64 && (a.N >= 1536 || (a.N >= 1024 && a.K <= 1024))) {
-      p.kind = 2;
-      p.bn = a.N >= 6144 ? 32 : 16;
-      p.bm = 64;
-      p.ksplit = a.K;
+    // few output tiles: the kernels whose waves split K (one launch, no K
+    // ranges; the rule and its measurements are wave_plan's)
+    const WavePlan w = wave_plan(a);
+    if (w.tile != WavePlan::NONE) {
+      p.kind = a.M <= 64 || a.rms_in ? 2 : 0;
+      p.bn = w.bn(); p.bm = w.bm(a.w_type); p.kg = w.waves(); p.stages = w.slots;
+      p.ksplit = nk * BK;
       return p;
     }
     // long-K products with enough 256 x 256 tiles: the large-tile kernel
@@ -1088,18 +962,6 @@ static void launch_big(const GemmArgs& a, int bm, hipStream_t s) {
   hipLaunchKernelGGL((gemm_big_kernel<MODE, NW, 256>), grid, dim3(NW * 64), 0, s, a);
 }
 
-template <int TN, int MODE>
-static void launch_skinny(const GemmArgs& a, hipStream_t s) {
-  dim3 grid((a.M + 63) / 64, (a.N + 16 * TN - 1) / (16 * TN), 1);
-  if constexpr (MODE == EPI_STORE || MODE == EPI_QKV || MODE == EPI_GEGLU || MODE == EPI_EULER) {
-    if (a.rms_in) {
-      hipLaunchKernelGGL((gemm_skinny_kernel<TN, MODE, 1>), grid, dim3(256), 0, s, a);
-      return;
-    }
-  }
-  hipLaunchKernelGGL((gemm_skinny_kernel<TN, MODE>), grid, dim3(256), 0, s, a);
-}
-
 template <int BN, int BM, int MODE>
 static void launch_mfma(const GemmArgs& a0, const GemmPlan& p, const NormArgs* fuse, hipStream_t s) {
   GemmArgs a = a0;
@@ -1129,7 +991,7 @@ static void launch_mfma(const GemmArgs& a0, const GemmPlan& p, const NormArgs* f
 template <int MODE>
 static void launch_mode(const GemmArgs& a, const GemmPlan& p, const NormArgs* fuse, hipStream_t s) {
   if (a.w_type == ET_F32) {
-    launch_gemm_wave_f32(a, s);
+    launch_gemm_wave(a, wave_plan(a), s);
     return;
   }
   if (p.kind == 3) {
@@ -1142,9 +1004,8 @@ static void launch_mode(const GemmArgs& a, const GemmPlan& p, const NormArgs* fu
     else launch_staged128<64, 2, MODE>(a, p, fuse, s);
     return;
   }
-  if (p.kind == 2) {
-    if (p.bn == 32) launch_skinny<2, MODE>(a, s);
-    else launch_skinny<1, MODE>(a, s);
+  if (p.kind == 2 || (p.kind == 0 && p.kg > 1)) {
+    launch_gemm_wave(a, wave_plan(a), s);
     return;
   }
   if (p.kind == 1) {

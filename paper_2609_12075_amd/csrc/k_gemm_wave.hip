@@ -1,17 +1,15 @@
-// Projection kernels whose wavefronts split K: for products whose output
-// tiles are small or few (the fp32 models; the action stage).
+// Projection kernels whose wavefronts split K: for products of few output
+// tiles (the action stage at small batch, the fp32 models).
 //
 // A block owns a tile of 16 TN weight rows x 16 TM activation rows, and each
 // of its NW waves computes the whole tile over its own part of K: K is cut
-// into chunks of 64 bytes per row, chunk c belongs to wave c % NW, and a wave
-// loads its fragments straight from global memory into the operand registers
-// of the matrix instructions, up to U chunks (all of them, for the action
-// stage's short K) in flight at once. No operand passes through LDS and the
-// K loop has no barrier: a product costs one or two memory round trips, and
-// within a block no operand element is loaded twice. The waves' partial tiles
-// are then added in LDS in a fixed order and the epilogue runs once per
-// output; what the epilogue reads (bias, old residual, row table, RoPE
-// angles) is loaded ahead of the K loop, beside the operands.
+// into chunks of 128 bytes per row, and chunk c belongs to wave c % NW. The
+// waves' partial tiles are added in LDS in a fixed order and the epilogue
+// runs once per output. What the epilogue reads (bias, old residual, row
+// table, RoPE angles) is loaded ahead of the operands, so that its memory
+// round trip runs beside theirs. No K ranges over blocks and so no second
+// launch: with one output tile per CU such a product is bound by one or two
+// memory round trips plus the launch, not by the matrix pipe.
 #include <algorithm>
 
 #include "gemm_epi.h"
@@ -21,28 +19,13 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
-// One 16-byte fragment of a row (E elements from k on), or with VEC false
-// (rows whose length, stride or base is not a multiple of 16 bytes) its
-// elements one by one, zeros past K.
-template <typename T, bool VEC>
-__device__ __forceinline__ u32x4 load_frag(const T* row, int k, int K) {
-  constexpr int E = 16 / sizeof(T);
-  if constexpr (VEC) {
-    return *reinterpret_cast<const u32x4*>(row + min(k, K - E));
-  } else {
-    f32x4 v;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = k + e < K ? (float)row[k + e] : 0.f;
-    return __builtin_bit_cast(u32x4, v);
-  }
-}
-
-// acc += W A^T over one chunk: a lane's 16 bytes of a row are the K elements
-// (lane / 16) E .. + E - 1 of the chunk, for both operands. In fp32 the four
-// 16 x 16 x 4 instructions take element e of every lane each (any assignment
-// of K to instructions is the same sum as long as both operands share it).
+// acc += W A^T over 64 bytes of K per row: a lane's 16 bytes of a row are the
+// elements (lane / 16) E .. + E - 1 (E per 16 bytes), for both operands. In
+// fp32 the four 16 x 16 x 4 instructions take element e of every lane each
+// (any assignment of K to instructions is the same sum as long as both
+// operands share it).
 template <typename T>
-__device__ __forceinline__ f32x4 mma_chunk(u32x4 w, u32x4 x, f32x4 acc) {
+__device__ __forceinline__ f32x4 mma16(u32x4 w, u32x4 x, f32x4 acc) {
   if constexpr (sizeof(T) == 2) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), acc, 0, 0, 0);
   } else {
@@ -53,38 +36,179 @@ __device__ __forceinline__ f32x4 mma_chunk(u32x4 w, u32x4 x, f32x4 acc) {
   }
 }
 
-// Planes of the partial tile kept in LDS at once: all NW, or half of them
-// (the upper waves hand theirs to the lower ones first) when all would leave
-// room for only one block per CU.
-constexpr int planes(int nw, int plane_bytes) { return nw * plane_bytes <= 80 * 1024 ? nw : nw / 2; }
+// The end both kernels share: the waves' partial tiles (lane holds rows n =
+// 16 i + 4 (lane / 16) + e of column m = 16 j + lane % 16) are added in LDS
+// and the epilogue runs. NP planes of the tile fit `red` at once; with fewer
+// planes than waves the upper half of the waves hands its tiles to the lower
+// half until the rest fits. The caller has loaded the epilogue's operands
+// (epi) for this thread's rows ms (valid where ok) when `fin` is set. RMS:
+// rsq[wave][row] receives the waves' sums of squares. All barriers are met by
+// every thread of the block.
+template <int TN, int TM, int NW>
+struct Tile {
+  static constexpr int BN = 16 * TN, BM = 16 * TM, NT = 64 * NW;
+  static constexpr int LDC = BN + (BN > 16 ? 4 : 0), PLANE = BM * LDC;      // floats
+  static constexpr int CPT = BN / 4, RS = NT / CPT, NIT = (BM + RS - 1) / RS;
+  // planes that fit `bytes` of LDS: NW or a half, quarter, ... of it
+  static constexpr int planes(int bytes) {
+    int n = NW;
+    while (n > 1 && n * PLANE * 4 > bytes) n /= 2;
+    return n;
+  }
+};
 
-// RMS (bf16): the RMSNorm of the activation rows folded into the product
-// (a.rms_in): every lane squares the fragments it loads.
-template <typename T, int TN, int TM, int NW, int U, int MODE, int RMS, bool VEC>
+template <int TN, int TM, int NW, int NP, int MODE, int RMS>
+__device__ __forceinline__ void finish_tile(const GemmArgs& a, f32x4 (&acc)[TN][TM], float (&rs)[TM], float* red, float* rsq,
+                                            const EpiRows<MODE, Tile<TN, TM, NW>::NIT>& epi,
+                                            const int (&ms)[Tile<TN, TM, NW>::NIT], const bool (&ok)[Tile<TN, TM, NW>::NIT],
+                                            bool fin, int m0, int n0, int wave) {
+  using G = Tile<TN, TM, NW>;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+  const int nc = (tid % G::CPT) * 4, r0 = tid / G::CPT;
+  auto at = [&](int plane, int i, int j) {
+    return reinterpret_cast<f32x4*>(red + plane * G::PLANE + (j * 16 + lr) * G::LDC + i * 16 + lq * 4);
+  };
+  if constexpr (RMS) {
+    // every activation element of the block's rows was read by exactly one
+    // lane: add the four lanes of a row here, the waves in wave order below
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+      rs[j] += __shfl_xor(rs[j], 16);
+      rs[j] += __shfl_xor(rs[j], 32);
+      if (lane < 16) rsq[wave * G::BM + j * 16 + lr] = rs[j];
+    }
+  }
+#pragma unroll
+  for (int n = NW; n > NP; n /= 2) {
+    if (wave >= n / 2 && wave < n) {
+#pragma unroll
+      for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) *at(wave - n / 2, i, j) = acc[i][j];
+    }
+    __syncthreads();
+    if (wave < n / 2) {
+#pragma unroll
+      for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) acc[i][j] += *at(wave, i, j);
+    }
+    if (n / 2 > NP) __syncthreads();      // (else each wave next writes the plane that it alone has read)
+  }
+  if (wave < NP) {
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j) *at(wave, i, j) = acc[i][j];
+  }
+  __syncthreads();
+  auto row_sum = [&](int mr, int nn) {
+    f32x4 t = *reinterpret_cast<const f32x4*>(red + mr * G::LDC + nn);
+#pragma unroll
+    for (int z = 1; z < NP; ++z) t += *reinterpret_cast<const f32x4*>(red + z * G::PLANE + mr * G::LDC + nn);
+    if constexpr (RMS) {
+      float s = rsq[mr];
+#pragma unroll
+      for (int z = 1; z < NW; ++z) s += rsq[z * G::BM + mr];
+      t = row_scale(t, rsqrtf(s / (float)a.rms_in + a.rms_eps));
+    }
+    return t;
+  };
+  if (a.epi_vec) {
+    if (!fin) return;
+    f32x4 t[G::NIT];
+#pragma unroll
+    for (int it = 0; it < G::NIT; ++it) t[it] = ok[it] ? row_sum(r0 + it * G::RS, nc) : f32x4{0.f, 0.f, 0.f, 0.f};
+    epi.finish(a, t, ms, ok, n0 + nc);
+    return;
+  }
+#pragma unroll 1
+  for (int c = tid; c < G::BM * G::CPT; c += G::NT) {
+    const int mr = c / G::CPT, nn = (c % G::CPT) * 4;
+    const f32x4 t = row_sum(mr, nn);
+    float v[4] = {t[0], t[1], t[2], t[3]};
+    epilogue4<MODE>(a, m0 + mr, n0 + nn, v);
+  }
+}
+
+// The rows of this thread in the vector epilogue; true when it has any.
+template <int TN, int TM, int NW>
+__device__ __forceinline__ bool my_rows(const GemmArgs& a, int m0, int n0, int (&ms)[Tile<TN, TM, NW>::NIT],
+                                        bool (&ok)[Tile<TN, TM, NW>::NIT]) {
+  using G = Tile<TN, TM, NW>;
+  const int nc = (threadIdx.x % G::CPT) * 4, r0 = threadIdx.x / G::CPT;
+#pragma unroll
+  for (int it = 0; it < G::NIT; ++it) {
+    ms[it] = m0 + r0 + it * G::RS;
+    ok[it] = r0 + it * G::RS < G::BM && ms[it] < a.M;
+  }
+  return a.epi_vec && n0 + nc < a.N && ok[0];
+}
+
+// ---------------------------------------------------------------- LDS ring per wave
+// Each wave moves its chunks global -> LDS with the direct loads into a ring
+// of S slots of its own (R = 16 (TN + TM) rows of 128 bytes; one load covers
+// 8 whole rows) and waits on its own loads only: the K loop has no barrier.
+// The 16-byte chunk c of row r sits in slot c ^ ((r / 2) % 8), which makes
+// the 16-row fragment reads conflict-free. Loading the fragments straight
+// into registers instead, without LDS, was measured at a quarter of the load
+// rate (~16 bytes a clock per CU: the matrix operand layout puts consecutive
+// lanes into different rows, so every lane is a cache line of its own):
+// 720 x 1920 by 50 rows 5.9 us against 3.8 us.
+// RMS: the RMSNorm of the activation rows folded into the product (a.rms_in);
+// every lane squares the fragments that it reads.
+template <typename T, int TN, int TM, int NW, int S, int MODE, int RMS>
 __global__ void __launch_bounds__(64 * NW) gemm_wave_kernel(GemmArgs a) {
-  constexpr int E = 16 / sizeof(T), CK = 4 * E;
-  constexpr int BN = 16 * TN, BM = 16 * TM, NT = 64 * NW;
-  constexpr int LDC = BN + (BN > 16 ? 4 : 0), PLANE = BM * LDC;
-  constexpr int NP = planes(NW, PLANE * 4);
-  __shared__ __attribute__((aligned(16))) float red[NP * PLANE];
-  __shared__ float rsq[RMS ? NW : 1][RMS ? BM : 1];
+  using G = Tile<TN, TM, NW>;
+  constexpr int E = 16 / sizeof(T), CK = 8 * E;          // elements per 16 bytes, per chunk
+  constexpr int R = G::BN + G::BM, LOADS = R / 8, SLOT = R * 128, RING = NW * S * SLOT;
+  constexpr int NP = G::planes(RING);
+  static_assert(NP * G::PLANE * 4 <= RING, "a plane must fit the ring");
+  static_assert(S == 1 || S == 2, "the waits below know rings of one or two slots");
+  // one LDS object: with a second one the compiler waits for every direct
+  // load before each fragment read
+  __shared__ __attribute__((aligned(1024))) char smem[RING + (RMS ? NW * G::BM * 4 : 0)];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int bx, by, bz;
   xcd_remap_grouped(bx, by, bz, 8);
   (void)bz;
-  const int m0 = bx * BM, n0 = by * BN, K = a.K;
-  const T* W = reinterpret_cast<const T*>(a.W);
-  const T* A = reinterpret_cast<const T*>(a.A);
-  const int lr = lane & 15, lk = (lane >> 4) * E;
+  const int m0 = bx * G::BM, n0 = by * G::BN, K = a.K;
+  const T* Z = reinterpret_cast<const T*>(a.zeros);
 
-  // this lane's fragment rows (clamped into the operands: what a row past
-  // the end computes is not stored)
-  const T *wrow[TN], *arow[TM];
+  int ms[G::NIT];
+  bool ok[G::NIT];
+  const bool fin = my_rows<TN, TM, NW>(a, m0, n0, ms, ok);
+  EpiRows<MODE, G::NIT> epi;
+  if (fin) epi.load(a, ms, ok, n0 + (tid % G::CPT) * 4);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // load j covers rows 8 j .. 8 j + 7 of the ring slot (weight rows, then
+  // activation rows): lane l moves slot l % 8 of row 8 j + l / 8. Rows past
+  // the operands read their last row (what they compute is not stored).
+  const T* src[LOADS];
+  int kof[LOADS];
 #pragma unroll
-  for (int i = 0; i < TN; ++i) wrow[i] = W + (long)min(n0 + i * 16 + lr, a.N - 1) * a.ldw;
+  for (int j = 0; j < LOADS; ++j) {
+    const int r = j * 8 + (lane >> 3);
+    kof[j] = ((lane & 7) ^ ((r >> 1) & 7)) * E;
+    src[j] = j * 8 < G::BN ? reinterpret_cast<const T*>(a.W) + (long)min(n0 + r, a.N - 1) * a.ldw
+                           : reinterpret_cast<const T*>(a.A) + (long)min(m0 + r - G::BN, a.M - 1) * a.lda;
+  }
+  char* ring = smem + wave * S * SLOT;
+  const int nch = (K + CK - 1) / CK;
+  const int per = nch > wave ? (nch - wave + NW - 1) / NW : 0;     // this wave's chunks
+  auto issue = [&](int i, int sl) {
+    const int kb = (wave + i * NW) * CK;
+    char* st = ring + sl * SLOT;
+    const bool whole = kb + CK <= K;
 #pragma unroll
-  for (int j = 0; j < TM; ++j) arow[j] = A + (long)min(m0 + j * 16 + lr, a.M - 1) * a.lda;
+    for (int j = 0; j < LOADS; ++j) {
+      // 16-byte pieces past K are read from the zero buffer
+      const void* g = whole || kb + kof[j] < K ? src[j] + kb + kof[j] : Z;
+      __builtin_amdgcn_global_load_lds(g, st + j * 1024, 16, 0, 0);
+    }
+  };
 
   f32x4 acc[TN][TM];
 #pragma unroll
@@ -94,155 +218,227 @@ __global__ void __launch_bounds__(64 * NW) gemm_wave_kernel(GemmArgs a) {
   float rs[TM], rs2[TM];
 #pragma unroll
   for (int j = 0; j < TM; ++j) rs[j] = rs2[j] = 0.f;
-
-  // the epilogue's rows and columns of this thread (vector epilogue)
-  constexpr int CPT = BN / 4, RS = NT / CPT, NIT = (BM + RS - 1) / RS;
-  const int nc = (tid % CPT) * 4, r0 = tid / CPT;
-  int ms[NIT];
-  bool ok[NIT];
 #pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    ms[it] = m0 + r0 + it * RS;
-    ok[it] = r0 + it * RS < BM && ms[it] < a.M;
+  for (int i = 0; i < S; ++i)
+    if (i < per) issue(i, i);
+  const int lr = lane & 15, lq = lane >> 4;
+  for (int i = 0; i < per; ++i) {
+    // chunk i has landed once only the next chunk's loads are pending
+    if (S == 2 && i + 1 < per) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const char* st = ring + (i % S) * SLOT;
+    u32x4 wf[2][TN], af[2][TM];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int c = q * 4 + lq;
+#pragma unroll
+      for (int t = 0; t < TN; ++t) {
+        const int r = 16 * t + lr;
+        wf[q][t] = *reinterpret_cast<const u32x4*>(st + r * 128 + ((c ^ ((r >> 1) & 7)) << 4));
+      }
+#pragma unroll
+      for (int t = 0; t < TM; ++t) {
+        const int r = G::BN + 16 * t + lr;
+        af[q][t] = *reinterpret_cast<const u32x4*>(st + r * 128 + ((c ^ ((r >> 1) & 7)) << 4));
+      }
+    }
+    // the fragments are in registers: their slot may be loaded again
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (i + S < per) issue(i + S, i % S);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if constexpr (RMS) {
+#pragma unroll
+        for (int t = 0; t < TM; ++t) sumsq8(__builtin_bit_cast(bf16x8, af[q][t]), rs[t], rs2[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int u = 0; u < TM; ++u) acc[t][u] = mma16<T>(wf[q][t], af[q][u], acc[t][u]);
+    }
   }
-  const bool fin = a.epi_vec && n0 + nc < a.N && ok[0];
-  EpiRows<MODE, NIT> epi;
+  __syncthreads();                         // every wave is done with its ring
+#pragma unroll
+  for (int j = 0; j < TM; ++j) rs[j] += rs2[j];
+  finish_tile<TN, TM, NW, NP, MODE, RMS>(a, acc, rs, reinterpret_cast<float*>(smem), reinterpret_cast<float*>(smem + RING),
+                                         epi, ms, ok, fin, m0, n0, wave);
+}
 
-  const int nch = (K + CK - 1) / CK;            // chunks; the last may be short
-  const bool tail = VEC && K % CK != 0;
+// ---------------------------------------------------------------- rows of any alignment
+// The same product with the fragments loaded straight into registers, U
+// 64-byte pieces of K in flight per wave: for rows that the direct loads
+// cannot take. bf16: operands whose base is not 16-byte aligned (K and the
+// strides are multiples of 8). fp32: rows whose length, stride or base is no
+// multiple of 16 bytes, read element by element.
+template <typename T, int TN, int TM, int NW, int U, int MODE, int RMS>
+__global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
+  using G = Tile<TN, TM, NW>;
+  constexpr int E = 16 / sizeof(T), CK = 4 * E;
+  constexpr int NP = G::planes(64 * 1024);
+  __shared__ __attribute__((aligned(16))) float red[NP * G::PLANE];
+  __shared__ float rsq[RMS ? NW * G::BM : 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int bx, by, bz;
+  xcd_remap_grouped(bx, by, bz, 8);
+  (void)bz;
+  const int m0 = bx * G::BM, n0 = by * G::BN, K = a.K;
+  const int lr = lane & 15, lk = (lane >> 4) * E;
+  int ms[G::NIT];
+  bool ok[G::NIT];
+  const bool fin = my_rows<TN, TM, NW>(a, m0, n0, ms, ok);
+  EpiRows<MODE, G::NIT> epi;
+  if (fin) epi.load(a, ms, ok, n0 + (tid % G::CPT) * 4);
+  const T *wrow[TN], *arow[TM];
+#pragma unroll
+  for (int i = 0; i < TN; ++i) wrow[i] = reinterpret_cast<const T*>(a.W) + (long)min(n0 + i * 16 + lr, a.N - 1) * a.ldw;
+#pragma unroll
+  for (int j = 0; j < TM; ++j) arow[j] = reinterpret_cast<const T*>(a.A) + (long)min(m0 + j * 16 + lr, a.M - 1) * a.lda;
+  // the lane's E elements from k on, zeros past K
+  auto frag = [&](const T* row, int k) {
+    if constexpr (sizeof(T) == 2) {
+      struct __attribute__((packed, aligned(2))) P { u32x4 v; };
+      return k < K ? reinterpret_cast<const P*>(row + k)->v : u32x4{0, 0, 0, 0};
+    } else {
+      f32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = k + e < K ? (float)row[k + e] : 0.f;
+      return __builtin_bit_cast(u32x4, v);
+    }
+  };
+  f32x4 acc[TN][TM];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float rs[TM], rs2[TM];
+#pragma unroll
+  for (int j = 0; j < TM; ++j) rs[j] = rs2[j] = 0.f;
+  const int nch = (K + CK - 1) / CK;
   for (int c0 = wave; c0 < nch; c0 += NW * U) {
     u32x4 wf[U][TN], af[U][TM];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (c0 + u * NW < nch) {
-        const int k = (c0 + u * NW) * CK + lk;
+      const int k = (c0 + u * NW) * CK + lk;
 #pragma unroll
-        for (int i = 0; i < TN; ++i) wf[u][i] = load_frag<T, VEC>(wrow[i], k, K);
+      for (int i = 0; i < TN; ++i) wf[u][i] = frag(wrow[i], k);
 #pragma unroll
-        for (int j = 0; j < TM; ++j) af[u][j] = load_frag<T, VEC>(arow[j], k, K);
-      }
+      for (int j = 0; j < TM; ++j) af[u][j] = frag(arow[j], k);
     }
-    if (c0 == wave && fin) epi.load(a, ms, ok, n0 + nc);
-    // keep every load of the round ahead of the matrix work
-    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int c = c0 + u * NW;
-      if (c < nch) {
-        if (tail && c == nch - 1) {
-          const bool kok = c * CK + lk < K;
+      if constexpr (RMS) {
 #pragma unroll
-          for (int i = 0; i < TN; ++i)
-            if (!kok) wf[u][i] = u32x4{0, 0, 0, 0};
-#pragma unroll
-          for (int j = 0; j < TM; ++j)
-            if (!kok) af[u][j] = u32x4{0, 0, 0, 0};
-        }
-        if constexpr (RMS) {
-#pragma unroll
-          for (int j = 0; j < TM; ++j) sumsq8(__builtin_bit_cast(bf16x8, af[u][j]), rs[j], rs2[j]);
-        }
-#pragma unroll
-        for (int i = 0; i < TN; ++i)
-#pragma unroll
-          for (int j = 0; j < TM; ++j) acc[i][j] = mma_chunk<T>(wf[u][i], af[u][j], acc[i][j]);
+        for (int j = 0; j < TM; ++j) sumsq8(__builtin_bit_cast(bf16x8, af[u][j]), rs[j], rs2[j]);
       }
-    }
-  }
-  if (wave >= nch && fin) epi.load(a, ms, ok, n0 + nc);   // a wave without a chunk
-
-  // lane holds rows n = 16 i + 4 (lane / 16) + e, column m = 16 j + lane % 16
-  auto put = [&](int plane) {
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-      for (int j = 0; j < TM; ++j)
-        *reinterpret_cast<f32x4*>(red + plane * PLANE + (j * 16 + lr) * LDC + i * 16 + (lane >> 4) * 4) = acc[i][j];
-  };
-  if constexpr (RMS) {
-    // every activation element of the block's rows was read by exactly one
-    // lane: add the four lanes of a row, later the waves in wave order
-#pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      rs[j] += rs2[j];
-      rs[j] += __shfl_xor(rs[j], 16);
-      rs[j] += __shfl_xor(rs[j], 32);
-      if (lane < 16) rsq[wave][j * 16 + lr] = rs[j];
-    }
-  }
-  if constexpr (NP < NW) {
-    if (wave >= NP) put(wave - NP);
-    __syncthreads();
-    if (wave < NP) {
 #pragma unroll
       for (int i = 0; i < TN; ++i)
 #pragma unroll
-        for (int j = 0; j < TM; ++j)
-          acc[i][j] += *reinterpret_cast<const f32x4*>(red + wave * PLANE + (j * 16 + lr) * LDC + i * 16 + (lane >> 4) * 4);
-      put(wave);                                // the plane this wave alone has just read
+        for (int j = 0; j < TM; ++j) acc[i][j] = mma16<T>(wf[u][i], af[u][j], acc[i][j]);
     }
-  } else {
-    put(wave);
   }
-  __syncthreads();
-  auto row_sum = [&](int mr, int nn) {
-    f32x4 t = *reinterpret_cast<const f32x4*>(red + mr * LDC + nn);
 #pragma unroll
-    for (int z = 1; z < NP; ++z) t += *reinterpret_cast<const f32x4*>(red + z * PLANE + mr * LDC + nn);
-    if constexpr (RMS) {
-      float s = rsq[0][mr];
-#pragma unroll
-      for (int z = 1; z < NW; ++z) s += rsq[z][mr];
-      t = row_scale(t, rsqrtf(s / (float)a.rms_in + a.rms_eps));
-    }
-    return t;
-  };
-  if (a.epi_vec) {
-    if (!fin) return;
-    f32x4 t[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) t[it] = ok[it] ? row_sum(r0 + it * RS, nc) : f32x4{0.f, 0.f, 0.f, 0.f};
-    epi.finish(a, t, ms, ok, n0 + nc);
+  for (int j = 0; j < TM; ++j) rs[j] += rs2[j];
+  finish_tile<TN, TM, NW, NP, MODE, RMS>(a, acc, rs, red, rsq, epi, ms, ok, fin, m0, n0, wave);
+}
+
+// ---------------------------------------------------------------- dispatch
+bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+template <int TN, int TM>
+dim3 grid_of(const GemmArgs& a) {
+  return dim3((a.M + 16 * TM - 1) / (16 * TM), (a.N + 16 * TN - 1) / (16 * TN), 1);
+}
+
+template <typename T, int TN, int TM, int NW, int S, int MODE, int RMS>
+void go(const GemmArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((gemm_wave_kernel<T, TN, TM, NW, S, MODE, RMS>), (grid_of<TN, TM>(a)), dim3(64 * NW), 0, s, a);
+}
+
+template <typename T, int MODE, int RMS>
+void launch(const GemmArgs& a, const WavePlan& p, hipStream_t s) {
+  switch (p.tile) {
+    case WavePlan::T16x16: go<T, 1, 1, 8, 2, MODE, RMS>(a, s); break;
+    case WavePlan::T32x16: go<T, 2, 1, 4, 2, MODE, RMS>(a, s); break;
+    case WavePlan::T32x32: p.slots == 1 ? go<T, 2, 2, 4, 1, MODE, RMS>(a, s) : go<T, 2, 2, 4, 2, MODE, RMS>(a, s); break;
+    case WavePlan::T32x64: go<T, 2, 4, 4, 2, MODE, RMS>(a, s); break;
+    case WavePlan::T64x64: go<T, 4, 4, 4, 2, MODE, RMS>(a, s); break;
+    case WavePlan::GATHER:
+      if constexpr (sizeof(T) == 2)
+        hipLaunchKernelGGL((gemm_gather_kernel<T, 1, 4, 8, 4, MODE, RMS>), (grid_of<1, 4>(a)), dim3(512), 0, s, a);
+      else
+        hipLaunchKernelGGL((gemm_gather_kernel<T, 1, 1, 8, 4, MODE, RMS>), (grid_of<1, 1>(a)), dim3(512), 0, s, a);
+      break;
+    case WavePlan::NONE: break;
+  }
+}
+
+template <int MODE>
+void launch_mode(const GemmArgs& a, const WavePlan& p, hipStream_t s) {
+  if (a.w_type == ET_F32) {
+    launch<float, MODE, 0>(a, p, s);
     return;
   }
-#pragma unroll 1
-  for (int c = tid; c < BM * CPT; c += NT) {
-    const int mr = c / CPT, nn = (c % CPT) * 4;
-    const f32x4 t = row_sum(mr, nn);
-    float v[4] = {t[0], t[1], t[2], t[3]};
-    epilogue4<MODE>(a, m0 + mr, n0 + nn, v);
+  if constexpr (MODE != EPI_RESID) {
+    if (a.rms_in) {
+      launch<bf16, MODE, 1>(a, p, s);
+      return;
+    }
   }
-}
-
-template <typename T, int TN, int TM, int NW, int U, int MODE, int RMS, bool VEC>
-void launch(const GemmArgs& a, hipStream_t s) {
-  dim3 grid((a.M + 16 * TM - 1) / (16 * TM), (a.N + 16 * TN - 1) / (16 * TN), 1);
-  hipLaunchKernelGGL((gemm_wave_kernel<T, TN, TM, NW, U, MODE, RMS, VEC>), grid, dim3(64 * NW), 0, s, a);
-}
-
-// fp32 tiles: the largest that still gives most CUs a block. 64 x 64 tiles
-// are bound by the matrix pipe (an 8-wave block loads 512 bytes and runs
-// 8192 multiply-adds per k), smaller ones by the latency of their one or two
-// round trips.
-template <int MODE>
-void launch_f32(const GemmArgs& a, hipStream_t s) {
-  auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  const bool vec = a.K >= 4 && a.K % 4 == 0 && a.lda % 4 == 0 && a.ldw % 4 == 0 && al(a.A) && al(a.W);
-  auto blocks = [&](long b) { return ((a.M + b - 1) / b) * ((a.N + b - 1) / b); };
-  if (!vec) launch<float, 1, 1, 8, 4, MODE, 0, false>(a, s);
-  else if (blocks(64) >= 192) launch<float, 4, 4, 8, 2, MODE, 0, true>(a, s);
-  else if (blocks(32) >= 192) launch<float, 2, 2, 8, 4, MODE, 0, true>(a, s);
-  else launch<float, 1, 1, 8, 8, MODE, 0, true>(a, s);
+  launch<bf16, MODE, 0>(a, p, s);
 }
 
 }  // namespace
 
-void launch_gemm_wave_f32(const GemmArgs& a, hipStream_t s) {
+int WavePlan::bn() const { return tile == T16x16 || tile == GATHER ? 16 : tile == T64x64 ? 64 : 32; }
+int WavePlan::bm(int w_type) const {
+  if (tile == GATHER) return w_type == ET_BF16 ? 64 : 16;
+  return tile == T32x32 ? 32 : tile == T32x64 || tile == T64x64 ? 64 : 16;
+}
+int WavePlan::waves() const { return tile == T16x16 || tile == GATHER ? 8 : 4; }
+
+WavePlan wave_plan(const GemmArgs& a) {
+  WavePlan p;
+  const bool f32 = a.w_type == ET_F32;
+  const int per16 = f32 ? 4 : 8;               // elements per 16 bytes
+  const bool direct = a.zeros && al16(a.A) && al16(a.W) && a.K % per16 == 0 && a.lda % per16 == 0 && a.ldw % per16 == 0;
+  if (!direct) {
+    // bf16: only what no other kernel takes in this state
+    if (f32 || (a.M <= 64 && a.zeros)) p.tile = WavePlan::GATHER;
+    return p;
+  }
+  auto blocks = [&](long bn, long bm) { return ((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
+  const long row_bytes = (long)a.K * 16 / per16;
+  constexpr long CUS = 256;
+  // The smallest tile whose blocks leave no CU a second one. Up to 2 KiB of K
+  // per row a 32 x 32 tile takes one ring slot (32 KiB of LDS, so that blocks
+  // share CUs) and serves up to 640 blocks. Beyond, the staged tiles that
+  // share each operand row among more of a block's waves are faster. Measured
+  // (us, this kernel against the plans used before it, replayed graph): 50
+  // rows, 1600 x 720 3.7 / 6.1, 720 x 960 3.3 / 6.0, 3840 x 720 4.1 / 5.6,
+  // 720 x 1920 3.8 / 6.6, 2560 x 1024 4.5 / 7.3, 8192 x 1024 6.1 / 9.3,
+  // 1024 x 4096 5.4 / 8.1; 400 rows, 720 x 960 4.9 / 7.2, 1024 x 2048 6.5 /
+  // 11.1, 1024 x 4096 11.0 / 14.6; past the limits, 400 rows, 2560 x 1024
+  // 10.3 / 10.0, 8192 x 1024 20 / 13.8.
+  const bool short_k = row_bytes <= 2048;
+  p.slots = 2;
+  const bool few_rows = a.M <= 64 && a.N >= 1536;
+  if (!f32 && a.K > 4096 && !few_rows) return p;      // long K: K ranges over blocks
+  if (blocks(16, 16) <= CUS) p.tile = WavePlan::T16x16;
+  else if (blocks(32, 16) <= CUS) p.tile = WavePlan::T32x16;
+  else if (blocks(32, 32) <= (short_k ? 640 : CUS)) p.tile = WavePlan::T32x32, p.slots = short_k ? 1 : 2;
+  else if (!short_k && blocks(32, 64) <= CUS) p.tile = WavePlan::T32x64;
+  else if (f32 || (!short_k && blocks(64, 64) <= CUS)) p.tile = WavePlan::T64x64;
+  else if (few_rows) p.tile = WavePlan::T32x64;       // (one row of tiles: nothing to share between blocks)
+  return p;
+}
+
+void launch_gemm_wave(const GemmArgs& a, const WavePlan& p, hipStream_t s) {
   switch (a.mode) {
-    case EPI_STORE: launch_f32<EPI_STORE>(a, s); break;
-    case EPI_RESID: launch_f32<EPI_RESID>(a, s); break;
-    case EPI_GEGLU: launch_f32<EPI_GEGLU>(a, s); break;
-    case EPI_QKV: launch_f32<EPI_QKV>(a, s); break;
-    case EPI_EULER: launch_f32<EPI_EULER>(a, s); break;
+    case EPI_STORE: launch_mode<EPI_STORE>(a, p, s); break;
+    case EPI_RESID: launch_mode<EPI_RESID>(a, p, s); break;
+    case EPI_GEGLU: launch_mode<EPI_GEGLU>(a, p, s); break;
+    case EPI_QKV: launch_mode<EPI_QKV>(a, p, s); break;
+    case EPI_EULER: launch_mode<EPI_EULER>(a, p, s); break;
   }
 }

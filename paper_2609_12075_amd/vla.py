@@ -250,8 +250,9 @@ class Model:
         if plan["kind"] in (1, 4):
             return (f"gemm_stage_kernelILi{plan['tile_n']}ELi{plan['tile_m']}ELi{plan['stages']}ELi{mode}"
                     f"ELi{plan['bk']}ELi{plan['kg']}ELi{plan['rms']}E")
-        if plan["kind"] == 2:
-            return f"gemm_skinny_kernelILi{plan['tile_n'] // 16}ELi{mode}ELi{plan['rms']}E"
+        if plan["kind"] == 2 or (plan["kind"] == 0 and plan["kg"] > 1):
+            return (f"gemm_wave_kernelIDF16bLi{plan['tile_n'] // 16}ELi{plan['tile_m'] // 16}ELi{plan['kg']}"
+                    f"ELi{plan['stages']}ELi{mode}ELi{plan['rms']}E")
         if plan["kind"] == 3:
             return f"gemm_big_kernelILi{mode}E"
         return f"gemm_mfma_kernelILi{plan['tile_n']}ELi{plan['tile_m']}EDF16bLi{mode}E"

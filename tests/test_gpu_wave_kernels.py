@@ -64,3 +64,50 @@ def test_attention_f32_edges(B, Hq, Hkv, Lq, hd, len0, len1):
     p = torch.softmax(q.double() @ k.transpose(2, 3) / hd ** 0.5, -1)
     ref = (p @ v).transpose(1, 2).reshape(B, Lq, Hq * hd)
     np.testing.assert_allclose(got.numpy(), ref.numpy(), rtol=1e-4, atol=2e-6)
+
+
+# bf16: one shape or more per tile of the plan (weight rows x activation rows
+# 16 x 16, 32 x 16, 32 x 32 with a one- and a two-slot ring, 32 x 64, 64 x 64),
+# with ragged last tiles, fewer chunks than waves, and K ending inside a chunk
+BF16_SHAPES = [(1, 16, 8), (17, 100, 72), (50, 1000, 1096), (40, 1700, 200), (61, 2000, 1016), (100, 1500, 1240),
+               (330, 1030, 1032), (300, 1300, 136), (520, 1600, 1032), (64, 9000, 4104)]
+
+
+def _plan_of(M, N, K, **kw):
+    from paper_2609_12075_amd import vla
+    p = vla.gemm_plan(M, N, K, 0, **kw)
+    return p["tile_n"], p["tile_m"], p["stages"]
+
+
+def test_bf16_shapes_cover_every_tile():
+    got = {_plan_of(*s, out_bf16=True) for s in BF16_SHAPES}
+    assert got >= {(16, 16, 2), (32, 16, 2), (32, 32, 1), (32, 32, 2), (32, 64, 2), (64, 64, 2)}, got
+
+
+@pytest.mark.parametrize("M,N,K", BF16_SHAPES)
+@pytest.mark.parametrize("rms", [False, True])
+def test_projection_bf16_edges(M, N, K, rms):
+    """Aligned operands (direct loads) and, up to 64 rows, operands whose base
+    is 2 bytes off a 16-byte boundary (the gather kernel) against fp64."""
+    import torch
+    from paper_2609_12075_amd import vla
+    log(f"[wave bf16] M={M} N={N} K={K} rms={rms} plan={_plan_of(M, N, K, rms=rms)}")
+    g = torch.Generator().manual_seed(M + N + K)
+    A = torch.randn(M, K, generator=g).bfloat16()
+    W = (torch.randn(N, K, generator=g) * 0.05).bfloat16()
+    bias = torch.randn(N, generator=g)
+    x = A.double()
+    scale = 1 / torch.sqrt((x * x).mean(1, keepdim=True) + 1e-6) if rms else 1.0
+    ref = (scale * (x @ W.double().t()) + bias.double()).numpy()
+
+    def off(t, by):          # the same matrix `by` bf16 elements past an aligned address
+        flat = torch.zeros(t.numel() + 8, dtype=t.dtype, device="cuda")
+        flat[by:by + t.numel()] = t.cuda().flatten()
+        return flat[by:by + t.numel()].view(t.shape)
+
+    for by in ((0, 1) if M <= 64 else (0,)):
+        a, w = off(A, by), off(W, by)
+        out = vla.debug_gemm_rms(a, w, bias=bias.cuda(), eps=1e-6) if rms else vla.debug_gemm(a, w, bias=bias.cuda())
+        torch.cuda.synchronize()
+        # fp32 sums of K exact bf16 products: a few times sqrt(K) roundings of a term
+        np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=1e-4, atol=1e-5 * (np.sqrt(K) * 0.05 + 1))
