@@ -516,165 +516,6 @@ gemm_stage_kernel(GemmArgs a) {
   }
 }
 
-// ---------------------------------------------------------------- large-tile kernel
-// For large products (the VLM stage): 256 x 256 output tiles, NW waves in a
-// (NW / 2) x 2 grid: 8 waves of 64 x 128 (12 fragment reads per 32 matrix
-// instructions) or 4 waves of 128 x 128 (16 reads per 64 instructions: half
-// the LDS read traffic per product of a 64 x 64 wave tile; LDS bandwidth,
-// which the operand stores into LDS share, is what bounds the smaller
-// tiles). Operands move global -> LDS with direct loads through two 64 KiB
-// stages (one block per CU); per output this loads half the bytes of a
-// 128 x 128 tile. Rows are XOR-swizzled as in the multi-stage kernel; the
-// second K chunk's fragment reads are interleaved with the first chunk's
-// products. The epilogue stages the fp32 tile through LDS in two halves of
-// 128 rows; with REG (GeGLU or a plain bf16 store, eight waves) it works from
-// the accumulators instead (reg_epilogue): a lane's fragment holds four
-// consecutive weight columns of one activation row (for GeGLU two whole
-// gate/up pairs, so the activation runs in registers), and the four lanes
-// that share a row trade their packed results so that each lane stores 16 or
-// 32 contiguous bytes. That takes the LDS round trip and its barriers out of
-// every tile (pi0-shaped gate/up, 6528 x 32768 x 2048: 775 -> 740 us; 3264
-// rows 407 -> 362 us; results identical).
-template <int MODE, int NW, int BM = 256, bool REG = false>
-__global__ void __launch_bounds__(NW * 64) gemm_big_kernel(GemmArgs a) {
-  constexpr int BN = 256, BK = 64, ROWB = BK * 2;
-  static_assert(BM == 256 || BM == 224, "activation tile of 256 or 224 rows");
-  constexpr int WGN = NW / 2;                                    // waves along the weight rows
-  constexpr int WTN = BN / WGN, WTM = BM / 2;                    // wave tile
-  constexpr int TN = WTN / 16, TM = WTM / 16;
-  static_assert(!REG || ((MODE == EPI_GEGLU || MODE == EPI_STORE) && TN == 4), "register epilogue: eight waves");
-  constexpr int STAGE_BYTES = (BN + BM) * ROWB;                  // 64 KiB (60 KiB)
-  constexpr int LDC = BN + 4;
-  constexpr int SMEM = REG || 2 * STAGE_BYTES > 128 * LDC * 4 ? 2 * STAGE_BYTES : 128 * LDC * 4;
-  constexpr int GPW = 32 / NW;                                   // 8-row groups per wave of the weight tile
-  constexpr int AG = BM / 8;                                     // 8-row groups of the activation tile
-  constexpr int GPWA = (AG + NW - 1) / NW;                       // ... per wave (the last may be short)
-  __shared__ __attribute__((aligned(1024))) char smem[SMEM];
-  auto Cs = reinterpret_cast<float (*)[LDC]>(smem);
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wn0 = (wave >> 1) * WTN, wm0 = (wave & 1) * WTM;
-  int bx, by, bz;
-  xcd_remap_grouped(bx, by, bz, 8);
-  const int n_blk = by * BN, m_blk = bx * BM;
-  const int K = a.K;
-  const int nk = (K + BK - 1) / BK;
-  const bf16* W = reinterpret_cast<const bf16*>(a.W);
-  const bf16* A = reinterpret_cast<const bf16*>(a.A);
-  const bf16* Z = reinterpret_cast<const bf16*>(a.zeros);
-
-  // 8-row groups: 32 of W and BM / 8 of A per stage (with 224 rows the
-  // last round of A groups covers half the waves; the count per wave differs,
-  // which the full waits below do not mind)
-  const int lrow = lane >> 3, slot = lane & 7;
-  auto issue = [&](int kt, int buf) {
-    char* st = smem + buf * STAGE_BYTES;
-#pragma unroll
-    for (int j = 0; j < GPW; ++j) {
-      const int grp = j * NW + wave, r = grp * 8 + lrow;
-      const int c = slot ^ ((r >> 1) & 7), k = kt * BK + c * 8, n = n_blk + r;
-      const bf16* src = (n < a.N && k < K) ? W + (long)n * a.ldw + k : Z;
-      __builtin_amdgcn_global_load_lds(src, st + grp * 8 * ROWB, 16, 0, 0);
-    }
-#pragma unroll
-    for (int j = 0; j < GPWA; ++j) {
-      const int grp = j * NW + wave, r = grp * 8 + lrow;
-      if (AG % NW != 0 && grp >= AG) break;
-      const int c = slot ^ ((r >> 1) & 7), k = kt * BK + c * 8, m = m_blk + r;
-      const bf16* src = (m < a.M && k < K) ? A + (long)m * a.lda + k : Z;
-      __builtin_amdgcn_global_load_lds(src, st + BN * ROWB + grp * 8 * ROWB, 16, 0, 0);
-    }
-  };
-
-  f32x4 acc[TN][TM];
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int lr = lane & 15, lq = lane >> 4;
-  if (nk > 0) issue(0, 0);
-  for (int kt = 0; kt < nk; ++kt) {
-    // stage kt landed (nothing later is pending yet), and every wave is done
-    // with stage kt - 1, whose buffer the next issue overwrites
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (kt + 1 < nk) issue(kt + 1, (kt + 1) & 1);
-    const char* st = smem + (kt & 1) * STAGE_BYTES;
-    bf16x8 wf[2][TN], af[2][TM];
-#pragma unroll
-    for (int kc = 0; kc < 2; ++kc) {
-      const int c = kc * 4 + lq;
-#pragma unroll
-      for (int i = 0; i < TN; ++i) {
-        const int r = wn0 + 16 * i + lr;
-        wf[kc][i] = *reinterpret_cast<const bf16x8*>(st + r * ROWB + ((c ^ ((r >> 1) & 7)) << 4));
-      }
-#pragma unroll
-      for (int j = 0; j < TM; ++j) {
-        const int r = wm0 + 16 * j + lr;
-        af[kc][j] = *reinterpret_cast<const bf16x8*>(st + BN * ROWB + r * ROWB + ((c ^ ((r >> 1) & 7)) << 4));
-      }
-    }
-#pragma unroll
-    for (int kc = 0; kc < 2; ++kc)
-#pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[kc][i], af[kc][j], acc[i][j], 0, 0, 0);
-    {
-      constexpr int NRD = TN + TM, NMF = TN * TM, R = NMF / NRD > 0 ? NMF / NRD : 1;
-      __builtin_amdgcn_sched_group_barrier(0x100, NRD, 0);      // chunk 0 reads
-#pragma unroll
-      for (int q = 0; q < NRD; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // one chunk-1 read
-        __builtin_amdgcn_sched_group_barrier(0x008, R, 0);      // R chunk-0 products
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 2 * NMF - NRD * R, 0);
-    }
-  }
-  if constexpr (REG) {
-    f32x4 bias[4];
-    reg_bias(a, n_blk + wn0, lane, bias);
-    reg_epilogue<MODE, TM>(a, acc, bias, n_blk + wn0, m_blk + wm0, lane);
-    return;
-  }
-  // epilogue in two halves of BM / 2 activation rows (waves with wm0 == WTM h)
-#pragma unroll 1
-  for (int h = 0; h < 2; ++h) {
-    __syncthreads();
-    if (wm0 == WTM * h) {
-#pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-          *reinterpret_cast<f32x4*>(&Cs[16 * j + lr][wn0 + 16 * i + (lane >> 4) * 4]) = acc[i][j];
-    }
-    __syncthreads();
-    if (a.epi_vec) {
-      tile_epilogue<MODE, BN, WTM, NW * 64, LDC, 1, 4>(a, &Cs[0][0], m_blk + WTM * h, n_blk, tid);
-      continue;
-    }
-#pragma unroll 1
-    for (int c = tid; c < WTM * (BN / 4); c += NW * 64) {
-      const int mr = c / (BN / 4), nc = (c % (BN / 4)) * 4;
-      f32x4 t = *reinterpret_cast<const f32x4*>(&Cs[mr][nc]);
-      float v[4] = {t[0], t[1], t[2], t[3]};
-      epilogue4<MODE>(a, m_blk + WTM * h + mr, n_blk + nc, v);
-    }
-  }
-}
-
-// The epilogue from registers (reg_epilogue) needs bf16 output, whole
-// 16-column groups, 16-byte aligned output rows and bias, and for a plain
-// store no row table, row groups or fp32/bf16 copy.
-static bool reg_epi_ok(const GemmArgs& a) {
-  auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  if (a.out_type != ET_BF16 || a.N % 16 != 0 || a.ldo % 8 != 0 || !al(a.out) || (a.bias && !al(a.bias))) return false;
-  if (a.mode == EPI_GEGLU) return true;
-  return a.mode == EPI_STORE && !a.tab && a.row_group <= 0 && !a.out2;
-}
-
 // ---------------------------------------------------------------- dispatch
 // Kernels are specialised on tile shape, activation type and epilogue; fp32
 // activations (the Euler state, conditioning vectors, robot state) only feed
@@ -709,27 +550,25 @@ static GemmPlan plan_base(const GemmArgs& a) {
       p.ksplit = nk * BK;
       return p;
     }
-    // long-K products with enough 256 x 256 tiles: the large-tile kernel
-    // (measured ahead of the staged tiles from K = 2048 on), unless its last
-    // round of tiles leaves the chip mostly idle where the 128 x 128 staged
-    // tiles fill theirs: per K-step of 64, a round of 256 large tiles (one
-    // per CU) measured 2.1 us and a round of 512 staged tiles (two per CU)
-    // 1.2 us (e.g. the 2560-wide QKV projection of 6528 rows: 260 large tiles
-    // in two rounds, 124 us, against 1020 staged tiles in two rounds, 76 us)
-    // The large tiles are 256 activation rows high, or 224 when no more
-    // rounds of tiles result: a 224-row tile measured 3-7 % faster than a
-    // 256-row one (not the 12.5 % of its area: each K-step's fixed costs
-    // dominate), e.g. the pi0-shaped MLP down projection at 6528 rows, 240
-    // such tiles in one round, 435 us against 450 us for 208 taller ones. The
-    // accumulation order of every output, and so the result, is the same
-    // for both heights.
-    // Below K = 2048 the large tiles' fixed costs weigh more: they are taken
+    // long-K products with enough 256 x 256 tiles: the large-tile kernel,
+    // unless its last round of tiles leaves the chip mostly idle where the
+    // 128 x 128 staged tiles fill theirs: per K-step of 64, a round of 256
+    // large tiles (one per CU) measured 1.62 us and a round of 512 staged
+    // tiles (two per CU) 1.2 us (e.g. the 2560-wide QKV projection of 6528
+    // rows: 260 large tiles in two rounds, 94 us, against 1020 staged tiles in
+    // two rounds, 67 us).
+    // The large tiles are 256 activation rows high, or 224 when that takes no
+    // more time: a 224-row tile measured 10 % faster than a 256-row one (its
+    // loads, not its matrix work, set the pace), e.g. the pi0-shaped MLP down
+    // projection at 6528 rows, 240 such tiles in one round, 366 us against 380
+    // us for 208 taller ones. The accumulation order of every output, and so
+    // the result, is the same for both heights.
+    // Below K = 2048 the tile's fixed costs weigh more: large tiles are taken
     // there only for an output stored from registers (reg_epi_ok) and a
-    // margin of 10 % (measured: the SmolVLA-shaped vision encoder's MLP up,
-    // 49152 x 3072 x 768, 270 -> 240 us; the pi0-shaped ViT MLP up at 6144
-    // rows, 73 -> 70 us; half-filled last rounds stay on the staged tiles)
+    // margin of 10 % (the pi0-shaped ViT MLP up at 6144 rows, 67 us against 74;
+    // half-filled last rounds stay on the staged tiles).
     const long t256 = blocks(256, 256), t224 = blocks(256, 224), t128 = blocks(128, 128);
-    const double c256 = (t256 + 255) / 256 * 2.1, c224 = (t224 + 255) / 256 * 2.1 * 0.95;
+    const double c256 = (t256 + 255) / 256 * 1.62, c224 = (t224 + 255) / 256 * 1.62 * 0.9;
     const double c_big = std::min(c256, c224), c_staged = (t128 + 511) / 512 * 1.2;
     const bool long_k = a.K >= 2048 && c_big <= c_staged;
     const bool short_k = a.K >= 512 && a.K < 2048 && reg_epi_ok(a) && c_big <= 0.9 * c_staged;
@@ -943,25 +782,6 @@ static void launch_staged128(const GemmArgs& a0, const GemmPlan& p, const NormAr
 }
 
 
-template <int MODE, int NW = 8>
-static void launch_big(const GemmArgs& a, int bm, hipStream_t s) {
-  if constexpr ((MODE == EPI_GEGLU || MODE == EPI_STORE) && NW == 8) {
-    if (reg_epi_ok(a)) {
-      dim3 grid((a.M + bm - 1) / bm, (a.N + 255) / 256, 1);
-      if (bm == 224) hipLaunchKernelGGL((gemm_big_kernel<MODE, NW, 224, true>), grid, dim3(NW * 64), 0, s, a);
-      else hipLaunchKernelGGL((gemm_big_kernel<MODE, NW, 256, true>), grid, dim3(NW * 64), 0, s, a);
-      return;
-    }
-  }
-  if (bm == 224) {
-    dim3 grid((a.M + 223) / 224, (a.N + 255) / 256, 1);
-    hipLaunchKernelGGL((gemm_big_kernel<MODE, NW, 224>), grid, dim3(NW * 64), 0, s, a);
-    return;
-  }
-  dim3 grid((a.M + 255) / 256, (a.N + 255) / 256, 1);
-  hipLaunchKernelGGL((gemm_big_kernel<MODE, NW, 256>), grid, dim3(NW * 64), 0, s, a);
-}
-
 template <int BN, int BM, int MODE>
 static void launch_mfma(const GemmArgs& a0, const GemmPlan& p, const NormArgs* fuse, hipStream_t s) {
   GemmArgs a = a0;
@@ -995,7 +815,7 @@ static void launch_mode(const GemmArgs& a, const GemmPlan& p, const NormArgs* fu
     return;
   }
   if (p.kind == 3) {
-    launch_big<MODE>(a, p.bm, s);
+    launch_gemm_big(a, p.bm, s);
     return;
   }
   if (p.kind == 4) {

@@ -254,7 +254,7 @@ class Model:
             return (f"gemm_wave_kernelIDF16bLi{plan['tile_n'] // 16}ELi{plan['tile_m'] // 16}ELi{plan['kg']}"
                     f"ELi{plan['stages']}ELi{mode}ELi{plan['rms']}E")
         if plan["kind"] == 3:
-            return f"gemm_big_kernelILi{mode}E"
+            return f"gemm_big_kernelILi{mode}ELi{plan['tile_m'] // 32}E"
         return f"gemm_mfma_kernelILi{plan['tile_n']}ELi{plan['tile_m']}EDF16bLi{mode}E"
 
     def denoise(self, batch, kv, noise, steps, actions_out, stream=None):
