@@ -111,3 +111,14 @@ def test_projection_bf16_edges(M, N, K, rms):
         torch.cuda.synchronize()
         # fp32 sums of K exact bf16 products: a few times sqrt(K) roundings of a term
         np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=1e-4, atol=1e-5 * (np.sqrt(K) * 0.05 + 1))
+
+
+# patch extraction by vectors of 4, 2 and 1 pixels, with (112 of 108) and
+# without columns to fill; end to end against the oracle
+@pytest.mark.parametrize("patch,hw,bf16", [(8, 24, False), (6, 12, True), (5, 15, False), (5, 15, True)])
+def test_patch_sizes(patch, hw, bf16):
+    from paper_2609_12075_amd import synth
+    from tests.test_gpu_parity import check_parity
+    cfg = synth.CONFIGS["tiny"].with_(name=f"tiny-p{patch}-{bf16}", patch=patch, img_hw=hw, n_img=2, action_dim=8,
+                                      dtype=synth.DTYPE_BF16 if bf16 else synth.DTYPE_F32)
+    check_parity(cfg, 3)
