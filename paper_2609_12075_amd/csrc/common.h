@@ -39,13 +39,14 @@ enum ElemType { ET_F32 = 0, ET_BF16 = 1 };
 // of logical indices (x fastest, then y, then z): blocks that share an
 // operand (consecutive x) then share that die's L2. A bijection on [0, T).
 __device__ __forceinline__ void xcd_remap(int& bx, int& by, int& bz) {
-  const long gx = gridDim.x, gy = gridDim.y, T = gx * gy * (long)gridDim.z;
-  const long L = blockIdx.x + gx * (blockIdx.y + gy * (long)blockIdx.z);
-  const long q = T / 8, r = T % 8, x = L % 8, j = L / 8;
-  const long u = x * q + (x < r ? x : r) + j;
-  bx = (int)(u % gx);
-  by = (int)((u / gx) % gy);
-  bz = (int)(u / (gx * gy));
+  // (32-bit: a grid of 2^32 blocks would have outputs past the card's memory)
+  const unsigned gx = gridDim.x, gy = gridDim.y, T = gx * gy * gridDim.z;
+  const unsigned L = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+  const unsigned q = T / 8, r = T % 8, x = L % 8, j = L / 8;
+  const unsigned u = x * q + (x < r ? x : r) + j, v = u / gx;
+  bx = (int)(u - v * gx);
+  bz = (int)(v / gy);
+  by = (int)(v - bz * gy);
 }
 
 // The same die assignment for a matrix product's (M tile, N tile, K range)
@@ -177,6 +178,11 @@ struct AttnArgs {
   // and softmax statistics, and a second kernel merges them in range order.
   float* ws; long ws_floats;
   int splits, kchunk;       // set by launch_attention
+  // set by launch_attention for the kernel whose waves split the keys: query
+  // heads per KV head, and reciprocals ceil(2^32 / d) (0: d = 1) of the grid's
+  // x and y sizes and of Lq
+  int G;
+  unsigned mul_x, mul_y, mul_q;
   const void* zeros;        // >= 16 zero bytes (fill of chunks past hd); required for bf16
 };
 void launch_attention(const AttnArgs& a, hipStream_t s);

@@ -16,12 +16,14 @@
 // with the key order inside each 32-key chunk permuted consistently on the
 // V side.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 
 namespace {
 
@@ -761,6 +763,327 @@ __global__ void __launch_bounds__(256 * KS) attn_v2_kernel(AttnArgs a) {
   }
 }
 
+// ---------------------------------------------------------------- waves split the keys
+// The same attention where the row tiles are few (the action stage, prefills
+// of one request): a block owns 16 rows and VD dims of the output, each of
+// its NW waves takes every NW-th tile of KT keys, and the waves' (max, sum,
+// output) are merged in LDS in wave order. A wave moves its tiles global ->
+// LDS with the direct loads into a K and a V slot of its own and waits for
+// its own loads only, so there is no barrier between the queries' and the
+// merge's, and each slot is loaded again as soon as its fragments are in
+// registers. VD < HDP: the blocks of a row tile share its output dims, each
+// forms all scores and reads its dims of V only (a block is bound by the
+// ~54 bytes a clock that a CU loads, so four blocks a row tile, K whole and a
+// quarter of V each, take 62 % of the time of one).
+// These launches take a few microseconds, of which instruction fetch is a
+// part (the code is cold in each): ragged tiles are loaded by a rolled loop,
+// and block and row indices come from multiplications with host-made
+// reciprocals.
+// V^T fragments of NU consecutive 16-dim subtiles of one 32-key chunk: rows
+// 4 grp + .. and 16 rows further, whose swizzle is the same, so the two reads
+// of a subtile differ by an immediate offset only. Written out with their
+// wait, because the compiler puts a wait for ALL pending global loads, the
+// direct loads of the next keys among them, before each use of the builtin.
+// (attn_v2_kernel keeps the builtin: its loads have landed by then, and with
+// waits of its own its matrix instructions overlap the reads less, 120 -> 131
+// us for the pi0-shaped prefill at batch 8.)
+template <int NU, int OFF, int HI>
+__device__ __forceinline__ void read_vt(bf16x8* vf, const unsigned* ad) {
+  static_assert(NU == 2 || NU == 4, "two or four subtiles");
+  bf16x4 l[4], h[4];
+  if constexpr (NU == 4) {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8 offset:%12\n\tds_read_b64_tr_b16 %1, %8 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %2, %9 offset:%12\n\tds_read_b64_tr_b16 %3, %9 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %4, %10 offset:%12\n\tds_read_b64_tr_b16 %5, %10 offset:%13\n\t"
+        "ds_read_b64_tr_b16 %6, %11 offset:%12\n\tds_read_b64_tr_b16 %7, %11 offset:%13\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(l[0]), "=&v"(h[0]), "=&v"(l[1]), "=&v"(h[1]), "=&v"(l[2]), "=&v"(h[2]), "=&v"(l[3]), "=&v"(h[3])
+        : "v"(ad[0]), "v"(ad[1]), "v"(ad[2]), "v"(ad[3]), "n"(OFF), "n"(OFF + HI)
+        : "memory");
+  } else {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %4 offset:%6\n\tds_read_b64_tr_b16 %1, %4 offset:%7\n\t"
+        "ds_read_b64_tr_b16 %2, %5 offset:%6\n\tds_read_b64_tr_b16 %3, %5 offset:%7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(l[0]), "=&v"(h[0]), "=&v"(l[1]), "=&v"(h[1])
+        : "v"(ad[0]), "v"(ad[1]), "n"(OFF), "n"(OFF + HI)
+        : "memory");
+  }
+#pragma unroll
+  for (int u = 0; u < NU; ++u) vf[u] = __builtin_shufflevector(l[u], h[u], 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// The same of a 16-key tile: one read a subtile, four subtiles.
+template <int NU, int OFF>
+__device__ __forceinline__ void read_vt16(bf16x4* vf, const unsigned* ad) {
+  static_assert(NU == 4, "four subtiles");
+  bf16x4 l[4];
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %4 offset:%8\n\tds_read_b64_tr_b16 %1, %5 offset:%8\n\t"
+      "ds_read_b64_tr_b16 %2, %6 offset:%8\n\tds_read_b64_tr_b16 %3, %7 offset:%8\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(l[0]), "=&v"(l[1]), "=&v"(l[2]), "=&v"(l[3])
+      : "v"(ad[0]), "v"(ad[1]), "v"(ad[2]), "v"(ad[3]), "n"(OFF)
+      : "memory");
+#pragma unroll
+  for (int u = 0; u < 4; ++u) vf[u] = l[u];
+}
+
+// The lane's byte offsets within a V tile for read_vt: subtile u reads from
+// of[u % 8] + (u / 8) 256 (the swizzle touches the low 16 chunks of a row).
+template <int HDP>
+__device__ __forceinline__ void vt_offsets(unsigned* of) {
+  using C = V2<HDP>;
+  const int lane = threadIdx.x & 63, lq = lane & 15, r = 4 * (lane >> 4) + (lq >> 2);
+#pragma unroll
+  for (int u = 0; u < (HDP / 16 < 8 ? HDP / 16 : 8); ++u)
+    of[u] = r * C::ROWB + (((2 * u + ((lq & 3) >> 1)) ^ C::swz(r)) << 4) + ((lq & 1) << 3);
+}
+
+// o += V^T P^T over the 32 or 16 keys of two fragments
+__device__ __forceinline__ f32x4 pv_mma(bf16x8 v, bf16x8 p, f32x4 o) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, p, o, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 pv_mma(bf16x4 v, bf16x4 p, f32x4 o) {
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(v4s, v), __builtin_bit_cast(v4s, p), o, 0, 0, 0);
+}
+
+__device__ __forceinline__ unsigned lds_addr(const char* p) {
+  return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char*)(p);
+}
+
+__device__ __forceinline__ unsigned fast_div(unsigned n, unsigned mul) { return mul ? __umulhi(n, mul) : n; }
+
+// Rows [0, n) of a tile of KT rows of HDP elements (row stride st bytes from
+// base) into LDS at dst; rows from n on and 16-byte chunks from byte `end` of
+// a row on are read from the zero buffer.
+template <int HDP, int KT>
+__device__ __forceinline__ void issue_tile(const char* base, long st, int n, int end, const char* Z, char* dst) {
+  using C = V2<HDP>;
+  constexpr int L = KT * C::ROWB / 1024, RPL = 64 / C::CR;   // direct loads, rows per load
+  const int lane = threadIdx.x & 63, lrow = lane / C::CR;
+  const unsigned lof = (unsigned)(lrow * st);
+  const long step = RPL * st;
+  auto chunk = [&](int i) { return (unsigned)((lane % C::CR) ^ C::swz(i * RPL + lrow)) * 16; };
+  if (n >= KT && end >= C::ROWB) {
+#pragma unroll
+    for (int i = 0; i < L; ++i, base += step) {
+      const void* p = base + (lof + chunk(i));
+      __builtin_amdgcn_global_load_lds(p, dst + i * 1024, 16, 0, 0);
+    }
+  } else {
+#pragma unroll 1
+    for (int i = 0; i < L; ++i, base += step) {
+      const int c = (int)chunk(i);
+      const void* p = i * RPL + lrow < n && c < end ? base + (lof + c) : Z;
+      __builtin_amdgcn_global_load_lds(p, dst + i * 1024, 16, 0, 0);
+    }
+  }
+}
+
+template <int HDP, int VD, int NW, int KT>
+__global__ void __launch_bounds__(64 * NW) attn_wave_kernel(AttnArgs a) {
+  using C = V2<HDP>;
+  using CV = V2<VD>;
+  constexpr int DS = HDP / VD;                     // blocks that share a row tile's output dims
+  constexpr int KB = KT * C::ROWB, VB = KT * CV::ROWB, QB = 16 * C::ROWB;
+  constexpr int LK = KB / 1024, LV = VB / 1024, LQ = QB / 1024;
+  constexpr int NST = KT / 16, NC = HDP / 32, ND = VD / 16;
+  static_assert(LQ <= NW && LV >= 1, "one query load a wave; a V tile fills a load");
+  constexpr int RING = QB + NW * (KB + VB), MERGE = NW * (ND * 1024 + 128);
+  __shared__ __attribute__((aligned(1024))) char smem[RING > MERGE ? RING : MERGE];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // die-aware order (xcd_remap): the row tiles of one (request, KV head) are
+  // consecutive logical blocks
+  const unsigned gx = gridDim.x, T = gx * gridDim.y * gridDim.z;
+  const unsigned Lb = blockIdx.x + gx * (blockIdx.y + gridDim.y * blockIdx.z);
+  const unsigned xr = T % 8, x = Lb % 8, ub = x * (T / 8) + (x < xr ? x : xr) + Lb / 8;
+  const unsigned vb = fast_div(ub, a.mul_x), b = fast_div(vb, a.mul_y);
+  const int bx = (int)(ub - vb * gx), g = (int)(vb - b * gridDim.y);
+  const int tile = bx / DS, d0 = bx % DS * VD;
+  const int rows = a.G * a.Lq, hd = a.hd;
+  const int lq = lane & 15, grp = lane >> 4;
+  const int len0 = a.seg[0].len, len1 = a.seg[1].len, nt0 = (len0 + KT - 1) / KT, nt = nt0 + (len1 + KT - 1) / KT;
+  const char* Z = reinterpret_cast<const char*>(a.zeros);
+  char* slot_q = smem + wave * 1024;
+  char* slot_k = smem + QB + wave * (KB + VB);
+  char* slot_v = slot_k + KB;
+
+  // a tile belongs to one segment
+  auto issue = [&](int t, auto is_v) {
+    const int which = t >= nt0;
+    const AttnSeg& sg = a.seg[which];
+    const int k0 = (which ? t - nt0 : t) * KT, n = (which ? len1 : len0) - k0;
+    if constexpr (decltype(is_v)::value) {
+      const char* base = reinterpret_cast<const char*>(sg.v) + (sg.v_sb * b + sg.v_sh * g + sg.v_si * k0 + d0) * 2;
+      issue_tile<VD, KT>(base, sg.v_si * 2, n, (hd - d0) * 2, Z, slot_v);
+    } else {
+      const char* base = reinterpret_cast<const char*>(sg.k) + (sg.k_sb * b + sg.k_sh * g + sg.k_si * k0) * 2;
+      issue_tile<HDP, KT>(base, sg.k_si * 2, n, hd * 2, Z, slot_k);
+    }
+  };
+  constexpr std::false_type is_k{};
+  constexpr std::true_type is_v{};
+  // row r of the block's tile: query head g G + r / Lq, query r % Lq
+  auto row_of = [&](int r, int& head, int& qi) {
+    const int jh = (int)fast_div((unsigned)r, a.mul_q);
+    head = g * a.G + jh;
+    qi = r - jh * a.Lq;
+  };
+
+  // the queries, 1 KiB a wave, in the layout of a K tile
+  if (wave < LQ) {
+    const int lr = wave * (64 / C::CR) + lane / C::CR, r = tile * 16 + lr, c = ((lane % C::CR) ^ C::swz(lr)) * 8;
+    int head, qi;
+    row_of(r, head, qi);
+    const void* p = r < rows && c < hd ? reinterpret_cast<const bf16*>(a.q) + (a.q_sb * b + a.q_sh * head + a.q_si * qi + c)
+                                       : reinterpret_cast<const bf16*>(Z);
+    __builtin_amdgcn_global_load_lds(p, slot_q, 16, 0, 0);
+  }
+  int t = wave;
+  if (t < nt) {
+    issue(t, is_k);
+    issue(t, is_v);
+    // (this wave's queries have landed once only its first tile is pending)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LK + LV) : "memory");
+  } else {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+  asm volatile("s_barrier" ::: "memory");
+  bf16x8 qf[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+    qf[c] = *reinterpret_cast<const bf16x8*>(smem + lq * C::ROWB + (((c * 4 + grp) ^ C::swz(lq)) << 4));
+
+  f32x4 o[ND];
+  float m_run = -INFINITY, l_run = 0.f;            // l_run: this lane's keys
+#pragma unroll
+  for (int u = 0; u < ND; ++u) o[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float sl2 = a.scale * 1.4426950408889634f;
+  constexpr int NU = ND < 4 ? ND : 4, NV8 = ND < 8 ? ND : 8;
+  unsigned ad[NV8];
+  vt_offsets<VD>(ad);
+#pragma unroll
+  for (int u = 0; u < NV8; ++u) ad[u] += lds_addr(slot_v);
+#pragma unroll 1
+  for (; t < nt; t += NW) {
+    const bool next = t + NW < nt;
+    const int n = t >= nt0 ? len1 - (t - nt0) * KT : len0 - t * KT;
+    // this tile's keys have landed once only its values' loads are pending
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LV) : "memory");
+    bf16x8 kf[NST][NC];
+#pragma unroll
+    for (int st = 0; st < NST; ++st) {
+      const int row = st * 16 + lq;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        kf[st][c] = *reinterpret_cast<const bf16x8*>(slot_k + row * C::ROWB + (((c * 4 + grp) ^ C::swz(row)) << 4));
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (next) issue(t + NW, is_k);
+    f32x4 sc[NST];
+#pragma unroll
+    for (int st = 0; st < NST; ++st) {
+      f32x4 s2 = {0.f, 0.f, 0.f, 0.f};             // two chains
+      sc[st] = s2;
+#pragma unroll
+      for (int c = 0; c < NC; c += 2) {
+        sc[st] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[st][c], qf[c], sc[st], 0, 0, 0);
+        if (c + 1 < NC) s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[st][c + 1], qf[c + 1], s2, 0, 0, 0);
+      }
+      sc[st] += s2;
+    }
+    if (n < KT) {
+#pragma unroll
+      for (int st = 0; st < NST; ++st)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (st * 16 + grp * 4 + e >= n) sc[st][e] = -INFINITY;
+    }
+    float mx = fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3]));
+#pragma unroll
+    for (int st = 1; st < NST; ++st) mx = fmaxf(mx, fmaxf(fmaxf(sc[st][0], sc[st][1]), fmaxf(sc[st][2], sc[st][3])));
+    mx = max_x32(max_x16(mx));
+    const float m_new = fmaxf(m_run, mx * sl2), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    m_run = m_new;
+    l_run *= alpha;
+    typedef __attribute__((ext_vector_type(KT / 4))) __bf16 frag;   // 4 or 8 keys of a lane
+    frag pf;
+#pragma unroll
+    for (int st = 0; st < NST; ++st)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[st][e], sl2, -m_new));
+        pf[4 * st + e] = (bf16)pv;
+        l_run += pv;
+      }
+#pragma unroll
+    for (int u = 0; u < ND; ++u) o[u] *= alpha;
+    // the values have landed once only the next keys' loads are pending
+    if (next) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LK) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // key slot jj of the second product's lane group grp is key 4 grp + jj
+    // (jj < 4) or 16 + 4 grp + jj - 4
+    frag vf[ND];
+    auto part = [&](auto h_) {
+      constexpr int u0 = decltype(h_)::value * NU;
+      if constexpr (u0 >= ND) return;
+      else if constexpr (KT == 16) read_vt16<NU, u0 / 8 * 256>(vf + u0, ad + u0 % 8);
+      else read_vt<NU, u0 / 8 * 256, 16 * CV::ROWB>(vf + u0, ad + u0 % 8);
+    };
+    part(std::integral_constant<int, 0>{});
+    part(std::integral_constant<int, 1>{});
+    part(std::integral_constant<int, 2>{});
+    part(std::integral_constant<int, 3>{});
+    if (next) issue(t + NW, is_v);
+#pragma unroll
+    for (int u = 0; u < ND; ++u) o[u] = pv_mma(vf[u], pf, o[u]);
+  }
+
+  // merge: the waves store their outputs and statistics (one without keys a
+  // maximum of -inf and zeros), then each wave adds a share of the 16-dim
+  // subtiles in wave order
+  l_run = sum_x32(sum_x16(l_run));
+  __syncthreads();                                 // every wave is done with its slots
+  float* mo = reinterpret_cast<float*>(smem);
+  float* mst = mo + NW * ND * 256;                 // [wave][16][2]
+#pragma unroll
+  for (int u = 0; u < ND; ++u) *reinterpret_cast<f32x4*>(mo + (wave * ND + u) * 256 + lane * 4) = o[u];
+  if (grp == 0) *reinterpret_cast<f32x2*>(mst + (wave * 16 + lq) * 2) = f32x2{m_run, l_run};
+  __syncthreads();
+  if (wave >= ND) return;
+  const int r = tile * 16 + lq;
+  int head, qi;
+  row_of(r, head, qi);
+  f32x2 ml[NW];
+  float w[NW], mm = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    ml[q] = *reinterpret_cast<const f32x2*>(mst + (q * 16 + lq) * 2);
+    mm = fmaxf(mm, ml[q][0]);
+  }
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    w[q] = __builtin_amdgcn_exp2f(ml[q][0] - mm);
+    l += ml[q][1] * w[q];
+  }
+  const float inv = 1.0f / l;
+  bf16* op = reinterpret_cast<bf16*>(a.o) + (a.o_sb * b + a.o_sh * head + a.o_si * qi);
+#pragma unroll
+  for (int u = wave; u < ND; u += NW) {
+    const int d = d0 + u * 16 + grp * 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < NW; ++q) acc += *reinterpret_cast<const f32x4*>(mo + (q * ND + u) * 256 + lane * 4) * w[q];
+    if (r < rows && d < hd)
+      *reinterpret_cast<bf16x4*>(op + d) =
+          bf16x4{(bf16)(acc[0] * inv), (bf16)(acc[1] * inv), (bf16)(acc[2] * inv), (bf16)(acc[3] * inv)};
+  }
+}
+
 }  // namespace
 
 // Launch plan of a bf16 attention. Direct-load kernel: key groups inside a
@@ -806,6 +1129,41 @@ static void attn_plan(const AttnArgs& a, int& splits, int& kchunk, int& ks) {
   splits = (ntiles + per - 1) / per;              // every range holds keys
 }
 
+// The kernel whose waves split the keys, where its blocks of 16 rows are few:
+// at most one a CU (head dims to 32: eight, whose 33 KiB of LDS share a CU;
+// over 128: two, one after the other), and up to 1024 keys (longer ranges:
+// split-KV over blocks). At head dim 256, two or four blocks share a row tile
+// where that leaves every CU at most one. Measured (us with the merge launch
+// of the other kernel; 290 keys, 5 KV heads of 64, 50 tokens: batch 1 and 4
+// 8.2 -> 5.5, batch 16, 800 blocks, 8.8 / 10.7; 866 keys, 1 KV head of 256,
+// 400 rows a request: batch 1 16.7 -> 10.0, 2 19.1 -> 10.6, 4 21.0 -> 13.4, 8
+// 25.5 -> 16.0; one request's prefill, 296 keys of 256 20.0 -> 9.5, 816 keys
+// 32.5 -> 25.4, batch 4 of the former, 592 blocks, 17.4 / 27; 296 keys of 32,
+// 17 rows, 32 heads: batch 3 7.7 -> 4.8, 32 15.0 -> 12.9; 256 keys of 72 8.8
+// -> 6.5, batch 3, 768 blocks, 9.2 / 15).
+static bool launch_wave(const AttnArgs& a, hipStream_t s) {
+  const int G = a.Hq / a.Hkv, keys = a.seg[0].len + a.seg[1].len;
+  const long tiles = ((long)G * a.Lq + 15) / 16, blocks = tiles * a.Hkv * a.B;
+  if (!a.zeros || keys > 1024 || blocks > (a.hd <= 32 ? 2048 : a.hd <= 128 ? 256 : 512)) return false;
+  const int ds = a.hd <= 128 || blocks * 2 > 256 ? 1 : blocks * 4 > 256 ? 2 : 4;
+  AttnArgs b = a;
+  b.splits = 1;
+  b.G = G;
+  const dim3 grid((unsigned)tiles * ds, a.Hkv, a.B);
+  // n / d = n mul >> 32 holds while n d < 2^32: at most 2048 blocks, of 16 rows
+  auto mul = [](unsigned d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + d - 1) / d); };
+  b.mul_x = mul(grid.x); b.mul_y = mul(grid.y); b.mul_q = mul(a.Lq);
+#define GO(H, V, N, K) hipLaunchKernelGGL((attn_wave_kernel<H, V, N, K>), grid, dim3(64 * N), 0, s, b)
+  if (a.hd <= 32) GO(32, 32, 8, 32);
+  else if (a.hd <= 64) GO(64, 64, 8, 32);
+  else if (a.hd <= 128) GO(128, 128, 8, 32);
+  else if (ds == 1) GO(256, 256, 8, 16);
+  else if (ds == 2) GO(256, 128, 8, 16);
+  else GO(256, 64, 12, 16);
+#undef GO
+  return true;
+}
+
 void launch_attention(const AttnArgs& a, hipStream_t s) {
   if (a.B <= 0 || a.Lq <= 0) return;
   if (a.et == ET_F32) {
@@ -821,6 +1179,7 @@ void launch_attention(const AttnArgs& a, hipStream_t s) {
   for (const AttnSeg& sg : a.seg)
     VLA_REQUIRE(64L * 2 * std::max(std::labs(sg.k_si), std::labs(sg.v_si)) + 2L * a.hd < (1L << 32),
                 "attention key row stride too large");
+  if (launch_wave(a, s)) return;
   AttnArgs b = a;
   int ks;
   attn_plan(a, b.splits, b.kchunk, ks);

@@ -122,3 +122,35 @@ def test_patch_sizes(patch, hw, bf16):
     cfg = synth.CONFIGS["tiny"].with_(name=f"tiny-p{patch}-{bf16}", patch=patch, img_hw=hw, n_img=2, action_dim=8,
                                       dtype=synth.DTYPE_BF16 if bf16 else synth.DTYPE_F32)
     check_parity(cfg, 3)
+
+
+# bf16 attention whose waves split the keys: every head-dim padding, output
+# dims whole and shared by two and four blocks, one key, whole and ragged last
+# tiles in both segments, more tiles than waves, rows that end inside a tile,
+# and on both sides of its limits (1024 keys; 256, 512 or 2048 blocks)
+@pytest.mark.parametrize("B,Hq,Hkv,Lq,hd,len0,len1", [
+    (1, 1, 1, 1, 8, 1, 0), (2, 32, 32, 17, 32, 296, 0), (3, 6, 2, 9, 24, 33, 5), (33, 32, 32, 17, 32, 40, 0),
+    (1, 15, 5, 50, 64, 240, 50), (2, 6, 2, 11, 40, 31, 1), (1, 5, 1, 50, 64, 1024, 0), (1, 5, 1, 50, 64, 1024, 1),
+    (1, 16, 16, 256, 72, 256, 0), (1, 16, 16, 257, 72, 64, 0), (1, 4, 2, 7, 128, 999, 17),
+    (1, 8, 1, 50, 256, 816, 50), (1, 2, 1, 3, 200, 17, 0), (2, 2, 2, 33, 136, 15, 3), (4, 8, 1, 50, 256, 97, 20),
+    (8, 8, 1, 50, 256, 64, 9), (1, 8, 1, 296, 256, 296, 0), (3, 8, 1, 400, 256, 50, 0)])
+def test_attention_bf16_edges(B, Hq, Hkv, Lq, hd, len0, len1):
+    import torch
+    from paper_2609_12075_amd import vla
+    log(f"[attn bf16] B={B} Hq={Hq} Hkv={Hkv} Lq={Lq} hd={hd} len0={len0} len1={len1}")
+    g = torch.Generator().manual_seed(hd + len0 + B)
+    rnd = lambda *s: torch.randn(*s, generator=g).bfloat16()
+    q, k0, v0 = rnd(B, Hq, Lq, hd), rnd(B, Hkv, len0, hd), rnd(B, Hkv, len0, hd)
+    k1, v1 = (rnd(B, Hkv, len1, hd), rnd(B, Hkv, len1, hd)) if len1 else (None, None)
+    c = lambda t: None if t is None else t.cuda()
+    got = vla.debug_attention(c(q), c(k0), c(v0), c(k1), c(v1)).cpu().double()
+    k, v = (x if y is None else torch.cat([x, y], 2) for x, y in ((k0, k1), (v0, v1)))
+    k, v = (x.double().repeat_interleave(Hq // Hkv, 1) for x in (k, v))
+    p = torch.softmax(q.double() @ k.transpose(2, 3) / hd ** 0.5, -1)
+    rows = lambda o: o.transpose(1, 2).reshape(B, Lq, Hq * hd)
+    ref, mag = rows(p @ v), rows(p @ v.abs())
+    # bf16 (8 significant bits) rounds each probability and the output by at
+    # most 2^-8 of itself (half a unit of 2^-7); fp32 scores, exponentials and
+    # sums add a few 2^-22 of the summed magnitudes
+    bound = 2.0 ** -8 * 1.01 * (mag + ref.abs())
+    assert ((got - ref).abs() <= bound).all(), float(((got - ref).abs() / bound).max())
