@@ -312,21 +312,53 @@ gemm_stage_kernel(GemmArgs a) {
   // this lane's row within a row group and its LDS slot; the slot holds
   // logical chunk (slot ^ swz(row)) of the row
   const int lrow = lane / CPR, slot = lane % CPR;
+  // EARLY (128 x 128 tiles): a stage is requested again as soon as its
+  // fragments are in registers, ahead of the products, so that two K-steps of
+  // loads are in flight and a wave waits for loads requested a whole K-step
+  // earlier; rows past the operands read their last row (what they compute is
+  // not stored), so that a load is one addition to an offset formed here. The
+  // smaller tiles (short products, more blocks a CU) lose 1-3 % by the longer
+  // start and the second barrier. ViT products of 9216 rows, 768 wide: VLM
+  // stage of the SmolVLA-shaped model with its vision encoder at batch 3 797
+  // -> 769 us.
+  constexpr bool EARLY = BN == 128 && BM == 128 && STAGES == 2 && KG == 1;
+  constexpr int AHEAD = EARLY ? 2 : STAGES - 1;         // stages requested ahead
+  const bool ktail = (K - kbeg) % BK != 0;
+  long off[EARLY ? LOADS : 1];
+  if constexpr (EARLY) {
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j) {
+      const int grp = (j < WG ? j : j - WG) * NWV + wave, r = grp * RPI + lrow;
+      off[j] = (j < WG ? (long)min(n_blk + r, a.N - 1) * a.ldw : (long)min(m_blk + r, a.M - 1) * a.lda) + kbeg +
+               (slot ^ ((r >> SWS) & (CPR - 1))) * 8;
+    }
+  }
   auto issue = [&](int kt, int buf) {
     char* st = smem + buf * STAGE_BYTES;
+    if constexpr (EARLY) {
+      const bool last = ktail && kt == nk - 1;
 #pragma unroll
-    for (int j = 0; j < WG; ++j) {
-      const int grp = j * NWV + wave, r = grp * RPI + lrow;
-      const int c = slot ^ ((r >> SWS) & (CPR - 1)), k = kbeg + kt * BK + c * 8, n = n_blk + r;
-      const bf16* src = (n < a.N && k < K) ? W + (long)n * a.ldw + k : Z;
-      __builtin_amdgcn_global_load_lds(src, st + grp * RPI * ROWB, 16, 0, 0);
-    }
+      for (int j = 0; j < LOADS; ++j) {
+        const int grp = (j < WG ? j : j - WG) * NWV + wave, r = grp * RPI + lrow;
+        const bf16* src = (j < WG ? W : A) + off[j] + kt * BK;
+        if (last && kbeg + kt * BK + (slot ^ ((r >> SWS) & (CPR - 1))) * 8 >= K) src = Z;
+        __builtin_amdgcn_global_load_lds(src, st + (j < WG ? 0 : BN * ROWB) + grp * RPI * ROWB, 16, 0, 0);
+      }
+    } else {
 #pragma unroll
-    for (int j = 0; j < AG; ++j) {
-      const int grp = j * NWV + wave, r = grp * RPI + lrow;
-      const int c = slot ^ ((r >> SWS) & (CPR - 1)), k = kbeg + kt * BK + c * 8, m = m_blk + r;
-      const bf16* src = (m < a.M && k < K) ? A + (long)m * a.lda + k : Z;
-      __builtin_amdgcn_global_load_lds(src, st + BN * ROWB + grp * RPI * ROWB, 16, 0, 0);
+      for (int j = 0; j < WG; ++j) {
+        const int grp = j * NWV + wave, r = grp * RPI + lrow;
+        const int c = slot ^ ((r >> SWS) & (CPR - 1)), k = kbeg + kt * BK + c * 8, n = n_blk + r;
+        const bf16* src = (n < a.N && k < K) ? W + (long)n * a.ldw + k : Z;
+        __builtin_amdgcn_global_load_lds(src, st + grp * RPI * ROWB, 16, 0, 0);
+      }
+#pragma unroll
+      for (int j = 0; j < AG; ++j) {
+        const int grp = j * NWV + wave, r = grp * RPI + lrow;
+        const int c = slot ^ ((r >> SWS) & (CPR - 1)), k = kbeg + kt * BK + c * 8, m = m_blk + r;
+        const bf16* src = (m < a.M && k < K) ? A + (long)m * a.lda + k : Z;
+        __builtin_amdgcn_global_load_lds(src, st + BN * ROWB + grp * RPI * ROWB, 16, 0, 0);
+      }
     }
   };
 
@@ -362,19 +394,19 @@ gemm_stage_kernel(GemmArgs a) {
     if (a.epi_reg && kg == 0) reg_resid_load<TN, TM>(a, n_blk + wn0, m_blk + wm0, lane, rold, rrb, rrg);
   }
 #pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s)
+  for (int s = 0; s < AHEAD; ++s)
     if (s < nk) issue(s, s);
   for (int kt = 0; kt < nk; ++kt) {
     // Stage kt has landed once at most the later stages' loads are pending;
     // then a plain barrier (no fence, which would wait for every pending
     // load): after it every wave's stage-kt data is in LDS and every wave has
     // consumed stage kt-1 (its fragments fed the matrix instructions).
-    if (kt + STAGES - 2 < nk) {
-      asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"((STAGES - 2) * LOADS) : "memory");
+    if (kt + AHEAD - 1 < nk) {
+      asm volatile("s_waitcnt vmcnt(%0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::"n"((AHEAD - 1) * LOADS) : "memory");
     } else {
       asm volatile("s_waitcnt vmcnt(0)\n\ts_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
-    if (kt + STAGES - 1 < nk) issue(kt + STAGES - 1, (kt + STAGES - 1) % STAGES);
+    if (!EARLY && kt + AHEAD < nk) issue(kt + AHEAD, (kt + AHEAD) % STAGES);
     const char* st = smem + (kt % STAGES) * STAGE_BYTES;
     // all of the group's fragments of the K-step, then the products; the
     // scheduler is told to interleave the second chunk's fragment reads with
@@ -395,6 +427,12 @@ gemm_stage_kernel(GemmArgs a) {
         af[q][j] = *reinterpret_cast<const bf16x8*>(st + BN * ROWB + r * ROWB + ((c ^ ((r >> SWS) & (CPR - 1))) << 4));
       }
     }
+    if (EARLY && kt + AHEAD < nk) {
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      issue(kt + AHEAD, kt % STAGES);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
     for (int q = 0; q < KCG; ++q)
 #pragma unroll
@@ -402,7 +440,7 @@ gemm_stage_kernel(GemmArgs a) {
 #pragma unroll
         for (int j = 0; j < TM; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[q][i], af[q][j], acc[i][j], 0, 0, 0);
-    if constexpr (KCG == 2) {
+    if constexpr (KCG == 2 && !EARLY) {
       constexpr int NRD = TN + TM, NMF = TN * TM, R = NMF / NRD > 0 ? NMF / NRD : 1;
       __builtin_amdgcn_sched_group_barrier(0x100, NRD, 0);      // chunk 0 reads
 #pragma unroll
