@@ -458,13 +458,24 @@ typedef short v4s __attribute__((ext_vector_type(4)));
 // A row statistic combined with the value of lane l ^ 16 (l ^ 32): one CDNA4
 // permlane swap of a value with itself exchanges the 16-lane rows (32-lane
 // halves), and its two results hold the lane's own value and its partner's.
+// The maximum that passes a NaN on (a row with a NaN score is NaN in either
+// case): gfx950 has it as one instruction of two or three operands, where
+// fmaxf first has to quiet each operand by an instruction of its own.
+__device__ __forceinline__ float vmax(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 __device__ __forceinline__ float max_x16(float v) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  return vmax(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 __device__ __forceinline__ float max_x32(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  return vmax(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <int N>
+__device__ __forceinline__ float max_of(const f32x4 (&s)[N]) {
+  float m = s[0][0];
+#pragma unroll
+  for (int i = 1; i < 4 * N; i += 2) m = i + 1 < 4 * N ? vmax(vmax(m, s[i / 4][i % 4]), s[(i + 1) / 4][(i + 1) % 4]) : vmax(m, s[i / 4][i % 4]);
+  return m;
 }
 __device__ __forceinline__ float sum_x16(float v) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -492,8 +503,10 @@ struct V2 {
   __device__ static constexpr int swz(int r) { return (r / RP) & SWM; }
 };
 
+// (two waves a SIMD at least: with the register file of one the compiler
+// keeps the products' results in the accumulation registers and copies them)
 template <int HDP, int KS>
-__global__ void __launch_bounds__(256 * KS) attn_v2_kernel(AttnArgs a) {
+__global__ void __launch_bounds__(256 * KS, 2) attn_v2_kernel(AttnArgs a) {
   using C = V2<HDP>;
   constexpr int BKV = C::BKV, ROWB = C::ROWB, TILE = C::TILE, CR = C::CR;
   constexpr int NW = 4 * KS;                       // waves per block
@@ -506,7 +519,7 @@ __global__ void __launch_bounds__(256 * KS) attn_v2_kernel(AttnArgs a) {
   constexpr int MERGE = KS > 1 ? (KS - 1) * 256 * MST * 4 : 0;
   __shared__ __attribute__((aligned(1024))) char smem[RING > MERGE ? RING : MERGE];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave >> 2, wrow = wave & 3;       // key group, row group
   const int S = a.splits > 1 ? a.splits : 1;
   int bx, by, bz;
@@ -653,12 +666,7 @@ __global__ void __launch_bounds__(256 * KS) attn_v2_kernel(AttnArgs a) {
         for (int i = 0; i < 4; ++i)
           if (k0 + st * 16 + grp * 4 + i >= kend) sc[st][i] = -INFINITY;
     }
-    float mx = fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3]));
-#pragma unroll
-    for (int st = 1; st < NST; ++st)
-      mx = fmaxf(mx, fmaxf(fmaxf(sc[st][0], sc[st][1]), fmaxf(sc[st][2], sc[st][3])));
-    mx = max_x32(max_x16(mx));
-    const float m_new = fmaxf(m_run, mx * sl2);
+    const float m_new = vmax(m_run, max_x32(max_x16(max_of(sc))) * sl2);
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
     float ps[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -669,8 +677,8 @@ __global__ void __launch_bounds__(256 * KS) attn_v2_kernel(AttnArgs a) {
         sc[st][i] = pv;
         ps[i] += pv;
       }
-    const float psum = sum_x32(sum_x16((ps[0] + ps[1]) + (ps[2] + ps[3])));
-    l_run = l_run * alpha + psum;
+    // (this lane's keys; the lanes of a row are added after the last tile)
+    l_run = l_run * alpha + ((ps[0] + ps[1]) + (ps[2] + ps[3]));
     m_run = m_new;
 #pragma unroll
     for (int u = 0; u < ND; ++u) o[u] *= alpha;
@@ -696,6 +704,8 @@ __global__ void __launch_bounds__(256 * KS) attn_v2_kernel(AttnArgs a) {
       }
     }
   }
+
+  l_run = sum_x32(sum_x16(l_run));
 
   if constexpr (KS > 1) {
     // merge the key groups into group 0, in group order: m = max m_q,
@@ -1008,11 +1018,7 @@ __global__ void __launch_bounds__(64 * NW) attn_wave_kernel(AttnArgs a) {
         for (int e = 0; e < 4; ++e)
           if (st * 16 + grp * 4 + e >= n) sc[st][e] = -INFINITY;
     }
-    float mx = fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3]));
-#pragma unroll
-    for (int st = 1; st < NST; ++st) mx = fmaxf(mx, fmaxf(fmaxf(sc[st][0], sc[st][1]), fmaxf(sc[st][2], sc[st][3])));
-    mx = max_x32(max_x16(mx));
-    const float m_new = fmaxf(m_run, mx * sl2), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    const float m_new = vmax(m_run, max_x32(max_x16(max_of(sc))) * sl2), alpha = __builtin_amdgcn_exp2f(m_run - m_new);
     m_run = m_new;
     l_run *= alpha;
     typedef __attribute__((ext_vector_type(KT / 4))) __bf16 frag;   // 4 or 8 keys of a lane
