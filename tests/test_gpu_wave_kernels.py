@@ -127,11 +127,12 @@ def test_patch_sizes(patch, hw, bf16):
 # bf16 attention whose waves split the keys: every head-dim padding, output
 # dims whole and shared by two and four blocks, one key, whole and ragged last
 # tiles in both segments, more tiles than waves, rows that end inside a tile,
-# and on both sides of its limits (1024 keys; 256, 512 or 2048 blocks)
+# and on both sides of its limits (1024 keys; 256, 512 or 2048 blocks); many
+# row tiles at head dims 72 and 80, whose last subtiles are skipped
 @pytest.mark.parametrize("B,Hq,Hkv,Lq,hd,len0,len1", [
     (1, 1, 1, 1, 8, 1, 0), (2, 32, 32, 17, 32, 296, 0), (3, 6, 2, 9, 24, 33, 5), (33, 32, 32, 17, 32, 40, 0),
     (1, 15, 5, 50, 64, 240, 50), (2, 6, 2, 11, 40, 31, 1), (1, 5, 1, 50, 64, 1024, 0), (1, 5, 1, 50, 64, 1024, 1),
-    (1, 16, 16, 256, 72, 256, 0), (1, 16, 16, 257, 72, 64, 0), (1, 4, 2, 7, 128, 999, 17),
+    (1, 16, 16, 256, 72, 256, 0), (1, 16, 16, 257, 72, 64, 0), (4, 16, 16, 257, 72, 70, 3), (17, 16, 16, 64, 80, 65, 0), (1, 4, 2, 7, 128, 999, 17),
     (1, 8, 1, 50, 256, 816, 50), (1, 2, 1, 3, 200, 17, 0), (2, 2, 2, 33, 136, 15, 3), (4, 8, 1, 50, 256, 97, 20),
     (8, 8, 1, 50, 256, 64, 9), (1, 8, 1, 296, 256, 296, 0), (3, 8, 1, 400, 256, 50, 0)])
 def test_attention_bf16_edges(B, Hq, Hkv, Lq, hd, len0, len1):
