@@ -136,8 +136,8 @@ struct GemmArgs {
   // RMSNorm folded into this projection (rms_in = d > 0): A holds rows x not
   // yet normalised and W the weights with the norm's gain folded into their
   // columns; row m of the product is scaled by rsqrt(sum_k x[m][k]^2 / d +
-  // rms_eps) before the epilogue, the sum taken from the bf16 A tiles the
-  // product reads (bf16 A and W, no K ranges)
+  // rms_eps) before the epilogue, the sum taken from the A tiles the product
+  // reads (A and W of one type, no K ranges)
   int rms_in; float rms_eps;
   // set by the launcher: the tile epilogue runs from the accumulators
   // (GeGLU or plain bf16 store on the 128-column staged tiles; no LDS pass)
@@ -242,8 +242,8 @@ void launch_transpose_convert(const float* src, int K, int N, void* dst, int ldk
                               const int* perm, hipStream_t s);
 void launch_convert(const float* src, long n, void* dst, int et, hipStream_t s);
 void launch_round_bf16_f32(const float* src, long n, float* dst, hipStream_t s);
-// W[n][k] = bf16(W[n][k] * g[k]) for n < N, k < K (bf16 rows of stride ldk)
-void launch_scale_cols_bf16(void* W, long N, int K, int ldk, const float* g, hipStream_t s);
+// W[n][k] = W[n][k] * g[k], rounded to the type et, for n < N, k < K (rows of stride ldk)
+void launch_scale_cols(void* W, int et, long N, int K, int ldk, const float* g, hipStream_t s);
 
 // Debug probe: each workgroup writes its hardware placement (XCC id, SE id,
 // CU id) to out[block] as one word: xcc << 16 | se << 8 | cu.

@@ -169,13 +169,14 @@ __global__ void round_bf16_kernel(const float* src, long n, float* dst) {
 
 // W[n][k] *= g[k] for the bf16 weight rows of a projection whose input row
 // norm is folded into it (k < K; row stride ldk), rounded back to bf16
-__global__ void scale_cols_bf16_kernel(bf16* W, long N, int K, int ldk, const float* g) {
+template <typename T>
+__global__ void scale_cols_kernel(T* W, long N, int K, int ldk, const float* g) {
   const long total = N * (long)K;
   for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
     const long n = e / K;
     const int k = (int)(e % K);
-    bf16& w = W[n * ldk + k];
-    w = (bf16)((float)w * g[k]);
+    T& w = W[n * ldk + k];
+    w = (T)((float)w * g[k]);
   }
 }
 
@@ -307,9 +308,10 @@ void launch_convert(const float* src, long n, void* dst, int et, hipStream_t s) 
   hipLaunchKernelGGL(convert_kernel, dim3(grid_for(n)), dim3(256), 0, s, src, n, dst, et);
 }
 
-void launch_scale_cols_bf16(void* W, long N, int K, int ldk, const float* g, hipStream_t s) {
-  hipLaunchKernelGGL(scale_cols_bf16_kernel, dim3(grid_for(N * (long)K)), dim3(256), 0, s, reinterpret_cast<bf16*>(W), N,
-                     K, ldk, g);
+void launch_scale_cols(void* W, int et, long N, int K, int ldk, const float* g, hipStream_t s) {
+  const dim3 grid(grid_for(N * (long)K));
+  if (et == ET_BF16) hipLaunchKernelGGL(scale_cols_kernel<bf16>, grid, dim3(256), 0, s, reinterpret_cast<bf16*>(W), N, K, ldk, g);
+  else hipLaunchKernelGGL(scale_cols_kernel<float>, grid, dim3(256), 0, s, reinterpret_cast<float*>(W), N, K, ldk, g);
 }
 
 void launch_round_bf16_f32(const float* src, long n, float* dst, hipStream_t s) {

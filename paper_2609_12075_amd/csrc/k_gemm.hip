@@ -910,9 +910,9 @@ void launch_gemm(const GemmArgs& a0, hipStream_t s) {
   if (a0.M <= 0 || a0.N <= 0) return;
   if (a0.a_type == ET_F32 && a0.w_type == ET_BF16 && a0.mode != EPI_STORE)
     throw VlaError{4, "fp32 activations with bf16 weights only feed plain stores"};
-  if (a0.rms_in && (a0.rms_in < 0 || a0.a_type != ET_BF16 || a0.w_type != ET_BF16 || !a0.zeros ||
+  if (a0.rms_in && (a0.rms_in < 0 || a0.a_type != a0.w_type || !a0.zeros ||
                     (a0.mode != EPI_STORE && a0.mode != EPI_QKV && a0.mode != EPI_GEGLU && a0.mode != EPI_EULER)))
-    throw VlaError{4, "a folded RMSNorm needs bf16 operands and a store, QKV, GeGLU or Euler epilogue"};
+    throw VlaError{4, "a folded RMSNorm needs operands of one type and a store, QKV, GeGLU or Euler epilogue"};
   if (a0.out2 && (a0.row_group > 0 || a0.ldo2 < a0.N || a0.out_type != ET_F32 ||
                   (a0.mode != EPI_STORE && a0.mode != EPI_RESID)))
     throw VlaError{4, "a bf16 copy needs an fp32 store or residual epilogue without row groups"};

@@ -36,6 +36,18 @@ __device__ __forceinline__ f32x4 mma16(u32x4 w, u32x4 x, f32x4 acc) {
   }
 }
 
+// s0 + s1 += the squares of a fragment's 16 bytes
+template <typename T>
+__device__ __forceinline__ void sumsq16(u32x4 v, float& s0, float& s1) {
+  if constexpr (sizeof(T) == 2) {
+    sumsq8(__builtin_bit_cast(bf16x8, v), s0, s1);
+  } else {
+    const f32x4 f = __builtin_bit_cast(f32x4, v);
+    s0 = fmaf(f[2], f[2], fmaf(f[0], f[0], s0));
+    s1 = fmaf(f[3], f[3], fmaf(f[1], f[1], s1));
+  }
+}
+
 // The end both kernels share: the waves' partial tiles (lane holds rows n =
 // 16 i + 4 (lane / 16) + e of column m = 16 j + lane % 16) are added in LDS
 // and the epilogue runs. NP planes of the tile fit `red` at once; with fewer
@@ -250,7 +262,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_wave_kernel(GemmArgs a) {
     for (int q = 0; q < 2; ++q) {
       if constexpr (RMS) {
 #pragma unroll
-        for (int t = 0; t < TM; ++t) sumsq8(__builtin_bit_cast(bf16x8, af[q][t]), rs[t], rs2[t]);
+        for (int t = 0; t < TM; ++t) sumsq16<T>(af[q][t], rs[t], rs2[t]);
       }
 #pragma unroll
       for (int t = 0; t < TN; ++t)
@@ -329,7 +341,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
     for (int u = 0; u < U; ++u) {
       if constexpr (RMS) {
 #pragma unroll
-        for (int j = 0; j < TM; ++j) sumsq8(__builtin_bit_cast(bf16x8, af[u][j]), rs[j], rs2[j]);
+        for (int j = 0; j < TM; ++j) sumsq16<T>(af[u][j], rs[j], rs2[j]);
       }
 #pragma unroll
       for (int i = 0; i < TN; ++i)
@@ -375,17 +387,16 @@ void launch(const GemmArgs& a, const WavePlan& p, hipStream_t s) {
 
 template <int MODE>
 void launch_mode(const GemmArgs& a, const WavePlan& p, hipStream_t s) {
-  if (a.w_type == ET_F32) {
-    launch<float, MODE, 0>(a, p, s);
-    return;
-  }
+  const bool f32 = a.w_type == ET_F32;
   if constexpr (MODE != EPI_RESID) {
     if (a.rms_in) {
-      launch<bf16, MODE, 1>(a, p, s);
+      if (f32) launch<float, MODE, 1>(a, p, s);
+      else launch<bf16, MODE, 1>(a, p, s);
       return;
     }
   }
-  launch<bf16, MODE, 0>(a, p, s);
+  if (f32) launch<float, MODE, 0>(a, p, s);
+  else launch<bf16, MODE, 0>(a, p, s);
 }
 
 }  // namespace

@@ -350,21 +350,20 @@ void vla_model_s::init(const vla_config& c, const float* w, size_t n, int dev) {
       }
       t2 = L.mat(Da, Da); t2_b = L.vec(Da);
       for (int l = 0; l < c.act_layers; ++l) act.push_back(gemma_layer(Da, Fa));
-      act_fold = et == ET_BF16;
-      if (act_fold) {
+      {
         for (LlmLayer& y : act) {
-          launch_scale_cols_bf16(y.qkv.p, y.qkv.N, Da, y.qkv.ldk, y.ln1, L.s);
-          launch_scale_cols_bf16(y.gu.p, y.gu.N, Da, y.gu.ldk, y.ln2, L.s);
+          launch_scale_cols(y.qkv.p, et, y.qkv.N, Da, y.qkv.ldk, y.ln1, L.s);
+          launch_scale_cols(y.gu.p, et, y.gu.N, Da, y.gu.ldk, y.ln2, L.s);
         }
         VLA_HIP(hipGetLastError());
         VLA_HIP(hipStreamSynchronize(L.s));
       }
       lnf = L.vec(Da);
       out = L.mat(Da, A); out_b = L.vec(A);
-      if (act_fold) {
+      {
         // the final RMSNorm's gain, folded like the layers' into the output
         // projection's columns
-        launch_scale_cols_bf16(out.p, out.N, Da, out.ldk, lnf, L.s);
+        launch_scale_cols(out.p, et, out.N, Da, out.ldk, lnf, L.s);
         VLA_HIP(hipGetLastError());
         VLA_HIP(hipStreamSynchronize(L.s));
       }
@@ -438,7 +437,7 @@ void vla_model_s::init(const vla_config& c, const float* w, size_t n, int dev) {
       const size_t Ma = (size_t)Bm * H;
       e = dalloc(Ma * Da * es); u = dalloc(Ma * Da * es);
       ha = (float*)dalloc(Ma * Da * 4);
-      za = dalloc(Ma * Da * es);
+      if (et == ET_BF16) za = dalloc(Ma * Da * es);
       qa = dalloc(Ma * Hq * es); ks = dalloc(Ma * Hk * es); vs = dalloc(Ma * Hk * es);
       oa = dalloc(Ma * Hq * es); gua = dalloc(Ma * Fa * es);
     }
@@ -698,6 +697,7 @@ void vla_model_s::enqueue_denoise(int B, const void* kv, const float* noise, int
 
   if (c.head_kind == VLA_HEAD_JOINT) {
     const int M = B * H, nq = c.n_q, nkv = c.n_kv, Fa = c.act_mlp;
+    const void* hz = za ? za : ha;
     const size_t per = (size_t)B * nkv * P * hd * es;
     for (int k = 0; k < N; ++k) {
       if (ain_t1.p) {
@@ -706,18 +706,16 @@ void vla_model_s::enqueue_denoise(int B, const void* kv, const float* noise, int
         store(gm(*this, ST,ain, M, x, A, ET_F32), e, Da, et, ain_b, ACT_NONE, s);
         store(gm(*this, ST,t1a, M, e, Da, et), u, Da, et, cc.tb + (size_t)k * Da, ACT_SILU, s);
       }
-      // za holds RMSNorm(ha) with the next projection's gain, or with the
-      // gains folded into the projections (act_fold) bf16(ha), which the
-      // projection normalises row by row
+      // the norms' gains are folded into the projections, which read the
+      // rows (ha, in a bf16 model its bf16 copy za) and normalise them
       GemmArgs g2 = gm(*this, ST,t2, M, u, Da, et);
-      if (act_fold) { g2.out2 = za; g2.ldo2 = Da; }
+      if (za) { g2.out2 = za; g2.ldo2 = Da; }
       store(g2, ha, Da, ET_F32, t2_b, ACT_NONE, s);
-      if (!act_fold) norm(M, Da, 0, ha, Da, za, Da, et, act[0].ln1, nullptr, eps, s);
       for (int l = 0; l < c.act_layers; ++l) {
         const LlmLayer& y = act[l];
-        GemmArgs q3 = gm(*this, ST,y.qkv, M, za, Da, et);
+        GemmArgs q3 = gm(*this, ST,y.qkv, M, hz, Da, et);
         q3.mode = EPI_QKV; q3.out_type = et;
-        if (act_fold) { q3.rms_in = Da; q3.rms_eps = eps; }
+        q3.rms_in = Da; q3.rms_eps = eps;
         QkvEpi& e3 = q3.qkv;
         e3.n_q = nq; e3.n_kv = nkv; e3.hd = hd; e3.seq = H; e3.pos0 = P; e3.rope_cs = rope_cs;
         e3.q = qa; e3.q_sb = (long)nq * H * hd; e3.q_sh = (long)H * hd; e3.q_si = hd;
@@ -733,29 +731,19 @@ void vla_model_s::enqueue_denoise(int B, const void* kv, const float* noise, int
         at.o = oa; at.o_sb = (long)H * Hq; at.o_sh = hd; at.o_si = Hq;
         launch_attention(at, s);
         GemmArgs go = gm(*this, ST,y.wo, M, oa, Hq, et);
-        if (act_fold) {
-          go.out2 = za; go.ldo2 = Da;
-          resid(go, ha, Da, nullptr, nullptr, s);
-        } else {
-          resid_norm(go, ha, Da, nullptr, nullptr, nargs(M, Da, 0, ha, Da, za, Da, et, y.ln2, nullptr, eps), s);
-        }
-        GemmArgs gg = gm(*this, ST,y.gu, M, za, Da, et);
+        if (za) { go.out2 = za; go.ldo2 = Da; }
+        resid(go, ha, Da, nullptr, nullptr, s);
+        GemmArgs gg = gm(*this, ST,y.gu, M, hz, Da, et);
         gg.mode = EPI_GEGLU; gg.out = gua; gg.ldo = Fa; gg.out_type = et;
-        if (act_fold) { gg.rms_in = Da; gg.rms_eps = eps; }
+        gg.rms_in = Da; gg.rms_eps = eps;
         launch_gemm(gg, s);
-        // then the next layer's RMSNorm, or the final one
         GemmArgs gd = gm(*this, ST,y.wd, M, gua, Fa, et);
-        if (act_fold) {
-          gd.out2 = za; gd.ldo2 = Da;
-          resid(gd, ha, Da, nullptr, nullptr, s);
-        } else {
-          const float* gn = l + 1 < c.act_layers ? act[l + 1].ln1 : lnf;
-          resid_norm(gd, ha, Da, nullptr, nullptr, nargs(M, Da, 0, ha, Da, za, Da, et, gn, nullptr, eps), s);
-        }
+        if (za) { gd.out2 = za; gd.ldo2 = Da; }
+        resid(gd, ha, Da, nullptr, nullptr, s);
       }
-      GemmArgs go = gm(*this, ST,out, M, za, Da, et);
+      GemmArgs go = gm(*this, ST,out, M, hz, Da, et);
       go.mode = EPI_EULER; go.out = x; go.ldo = A; go.out_type = ET_F32; go.bias = out_b; go.dt = dt;
-      if (act_fold) { go.rms_in = Da; go.rms_eps = eps; }   // the final norm, folded
+      go.rms_in = Da; go.rms_eps = eps;   // the final norm, folded
       launch_gemm(go, s);
     }
     return;
@@ -900,9 +888,9 @@ GemmArgs vla_model_s::stage_gemm(int which, int B, int layer) const {
       break;
     case 2:   // action stage: layer MLP up (GeGLU for the joint expert, GELU for the DiT)
       if (c.head_kind == VLA_HEAD_JOINT) {
-        g = gm(*this, ST,act[la].gu, B * H, za, Da, et);
+        g = gm(*this, ST,act[la].gu, B * H, za ? za : ha, Da, et);
         g.mode = EPI_GEGLU; g.out = gua; g.ldo = c.act_mlp; g.out_type = et;
-        if (act_fold) { g.rms_in = Da; g.rms_eps = c.norm_eps; }
+        g.rms_in = Da; g.rms_eps = c.norm_eps;
       } else {
         g = gm(*this, ST,dit[la].w1, B * Ltok, zd, Da, et);
         g.mode = EPI_STORE; g.act = ACT_GELU; g.bias = dit[la].b1; g.out = mlp; g.ldo = c.act_mlp; g.out_type = et;
@@ -912,11 +900,9 @@ GemmArgs vla_model_s::stage_gemm(int which, int B, int layer) const {
       if (c.head_kind == VLA_HEAD_JOINT) {
         g = gm(*this, ST,act[la].wd, B * H, gua, c.act_mlp, et);
         g.mode = EPI_RESID; g.out = ha; g.ldo = Da; g.out_type = ET_F32;
-        // with folded gains the layers write the bf16 copy that the next
-        // layer's QKV (the last: the output projection) normalises; without
-        // them a norm follows
-        if (act_fold) { g.out2 = za; g.ldo2 = Da; }
-        else g.norm_follows = 1;
+        // the bf16 copy that the next layer's QKV (the last: the output
+        // projection) normalises
+        if (za) { g.out2 = za; g.ldo2 = Da; }
       } else {
         g = gm(*this, ST,dit[la].w2, B * Ltok, mlp, c.act_mlp, et);
         g.mode = EPI_RESID; g.bias = dit[la].b2; g.out = X; g.ldo = Da; g.out_type = ET_F32;

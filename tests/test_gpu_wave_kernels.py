@@ -155,3 +155,13 @@ def test_attention_bf16_edges(B, Hq, Hkv, Lq, hd, len0, len1):
     # sums add a few 2^-22 of the summed magnitudes
     bound = 2.0 ** -8 * 1.01 * (mag + ref.abs())
     assert ((got - ref).abs() <= bound).all(), float(((got - ref).abs() / bound).max())
+
+
+# fp32 models whose action expert normalises its input rows inside the
+# projections: widths below, at and past a K chunk of the eight waves, batches
+# whose rows end inside a tile
+@pytest.mark.parametrize("d,horizon,batch", [(64, 3, 1), (96, 8, 3), (320, 17, 2)])
+def test_f32_folded_norms(d, horizon, batch):
+    from paper_2609_12075_amd import synth
+    from tests.test_gpu_parity import check_parity
+    check_parity(synth.CONFIGS["tiny"].with_(name=f"tiny-d{d}-h{horizon}", act_d=d, horizon=horizon), batch)
