@@ -362,7 +362,8 @@ __global__ void __launch_bounds__(512) attn_f32_kernel(AttnArgs a) {
                 : reinterpret_cast<const float*>(s.k) + (long)b * s.k_sb + (long)g * s.k_sh + (long)kk * s.k_si;
   };
   for (int t = wave; t < nt; t += NW) {
-    // keys past the end read the last key's rows; their scores become -inf
+    // keys past the end read the last key's rows; their scores become -inf and
+    // their values zeros
     const float* kp = row(min(t * 16 + lr, total - 1), false);
     f32x4 kf[NC], vf[NC];                            // vf[c][e]: V[key 4 lk + e][16 c + lr]
 #pragma unroll
@@ -372,6 +373,14 @@ __global__ void __launch_bounds__(512) attn_f32_kernel(AttnArgs a) {
       const float* vp = row(min(t * 16 + lk * 4 + e, total - 1), true);
 #pragma unroll
       for (int c = 0; c < NC; ++c) vf[c][e] = c * 16 + lr < hd ? vp[c * 16 + lr] : 0.f;
+    }
+    // (probability 0 times an infinity of the last key would be a NaN)
+    if (t * 16 + 16 > total) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          if (t * 16 + lk * 4 + e >= total) vf[c][e] = 0.f;
     }
     f32x4 sc = zero;
 #pragma unroll
