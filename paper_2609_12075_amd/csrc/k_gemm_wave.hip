@@ -50,26 +50,18 @@ __device__ __forceinline__ void sumsq16(u32x4 v, float& s0, float& s1) {
 
 // The end both kernels share: the waves' partial tiles (lane holds rows n =
 // 16 i + 4 (lane / 16) + e of column m = 16 j + lane % 16) are added in LDS
-// and the epilogue runs. NP planes of the tile fit `red` at once; with fewer
-// planes than waves the upper half of the waves hands its tiles to the lower
-// half until the rest fits. The caller has loaded the epilogue's operands
-// (epi) for this thread's rows ms (valid where ok) when `fin` is set. RMS:
-// rsq[wave][row] receives the waves' sums of squares. All barriers are met by
-// every thread of the block.
+// and the epilogue runs; `red` holds a plane of the tile per wave. The caller
+// has loaded the epilogue's operands (epi) for this thread's rows ms (valid
+// where ok) when `fin` is set. RMS: rsq[wave][row] receives the waves' sums of
+// squares. The barrier is met by every thread of the block.
 template <int TN, int TM, int NW>
 struct Tile {
   static constexpr int BN = 16 * TN, BM = 16 * TM, NT = 64 * NW;
   static constexpr int LDC = BN + (BN > 16 ? 4 : 0), PLANE = BM * LDC;      // floats
   static constexpr int CPT = BN / 4, RS = NT / CPT, NIT = (BM + RS - 1) / RS;
-  // planes that fit `bytes` of LDS: NW or a half, quarter, ... of it
-  static constexpr int planes(int bytes) {
-    int n = NW;
-    while (n > 1 && n * PLANE * 4 > bytes) n /= 2;
-    return n;
-  }
 };
 
-template <int TN, int TM, int NW, int NP, int MODE, int RMS>
+template <int TN, int TM, int NW, int MODE, int RMS>
 __device__ __forceinline__ void finish_tile(const GemmArgs& a, f32x4 (&acc)[TN][TM], float (&rs)[TM], float* red, float* rsq,
                                             const EpiRows<MODE, Tile<TN, TM, NW>::NIT>& epi,
                                             const int (&ms)[Tile<TN, TM, NW>::NIT], const bool (&ok)[Tile<TN, TM, NW>::NIT],
@@ -77,9 +69,6 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& a, f32x4 (&acc)[TN][
   using G = Tile<TN, TM, NW>;
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
   const int nc = (tid % G::CPT) * 4, r0 = tid / G::CPT;
-  auto at = [&](int plane, int i, int j) {
-    return reinterpret_cast<f32x4*>(red + plane * G::PLANE + (j * 16 + lr) * G::LDC + i * 16 + lq * 4);
-  };
   if constexpr (RMS) {
     // every activation element of the block's rows was read by exactly one
     // lane: add the four lanes of a row here, the waves in wave order below
@@ -91,33 +80,15 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& a, f32x4 (&acc)[TN][
     }
   }
 #pragma unroll
-  for (int n = NW; n > NP; n /= 2) {
-    if (wave >= n / 2 && wave < n) {
+  for (int i = 0; i < TN; ++i)
 #pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j) *at(wave - n / 2, i, j) = acc[i][j];
-    }
-    __syncthreads();
-    if (wave < n / 2) {
-#pragma unroll
-      for (int i = 0; i < TN; ++i)
-#pragma unroll
-        for (int j = 0; j < TM; ++j) acc[i][j] += *at(wave, i, j);
-    }
-    if (n / 2 > NP) __syncthreads();      // (else each wave next writes the plane that it alone has read)
-  }
-  if (wave < NP) {
-#pragma unroll
-    for (int i = 0; i < TN; ++i)
-#pragma unroll
-      for (int j = 0; j < TM; ++j) *at(wave, i, j) = acc[i][j];
-  }
+    for (int j = 0; j < TM; ++j)
+      *reinterpret_cast<f32x4*>(red + wave * G::PLANE + (j * 16 + lr) * G::LDC + i * 16 + lq * 4) = acc[i][j];
   __syncthreads();
   auto row_sum = [&](int mr, int nn) {
     f32x4 t = *reinterpret_cast<const f32x4*>(red + mr * G::LDC + nn);
 #pragma unroll
-    for (int z = 1; z < NP; ++z) t += *reinterpret_cast<const f32x4*>(red + z * G::PLANE + mr * G::LDC + nn);
+    for (int z = 1; z < NW; ++z) t += *reinterpret_cast<const f32x4*>(red + z * G::PLANE + mr * G::LDC + nn);
     if constexpr (RMS) {
       float s = rsq[mr];
 #pragma unroll
@@ -174,8 +145,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_wave_kernel(GemmArgs a) {
   using G = Tile<TN, TM, NW>;
   constexpr int E = 16 / sizeof(T), CK = 8 * E;          // elements per 16 bytes, per chunk
   constexpr int R = G::BN + G::BM, LOADS = R / 8, SLOT = R * 128, RING = NW * S * SLOT;
-  constexpr int NP = G::planes(RING);
-  static_assert(NP * G::PLANE * 4 <= RING, "a plane must fit the ring");
+  static_assert(NW * G::PLANE * 4 <= RING, "the waves' planes must fit the ring");
   static_assert(S == 1 || S == 2, "the waits below know rings of one or two slots");
   // one LDS object: with a second one the compiler waits for every direct
   // load before each fragment read
@@ -273,7 +243,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_wave_kernel(GemmArgs a) {
   __syncthreads();                         // every wave is done with its ring
 #pragma unroll
   for (int j = 0; j < TM; ++j) rs[j] += rs2[j];
-  finish_tile<TN, TM, NW, NP, MODE, RMS>(a, acc, rs, reinterpret_cast<float*>(smem), reinterpret_cast<float*>(smem + RING),
+  finish_tile<TN, TM, NW, MODE, RMS>(a, acc, rs, reinterpret_cast<float*>(smem), reinterpret_cast<float*>(smem + RING),
                                          epi, ms, ok, fin, m0, n0, wave);
 }
 
@@ -287,8 +257,7 @@ template <typename T, int TN, int TM, int NW, int U, int MODE, int RMS>
 __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   using G = Tile<TN, TM, NW>;
   constexpr int E = 16 / sizeof(T), CK = 4 * E;
-  constexpr int NP = G::planes(64 * 1024);
-  __shared__ __attribute__((aligned(16))) float red[NP * G::PLANE];
+  __shared__ __attribute__((aligned(16))) float red[NW * G::PLANE];
   __shared__ float rsq[RMS ? NW * G::BM : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int bx, by, bz;
@@ -351,7 +320,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   }
 #pragma unroll
   for (int j = 0; j < TM; ++j) rs[j] += rs2[j];
-  finish_tile<TN, TM, NW, NP, MODE, RMS>(a, acc, rs, red, rsq, epi, ms, ok, fin, m0, n0, wave);
+  finish_tile<TN, TM, NW, MODE, RMS>(a, acc, rs, red, rsq, epi, ms, ok, fin, m0, n0, wave);
 }
 
 // ---------------------------------------------------------------- dispatch
