@@ -268,7 +268,7 @@ __global__ void __launch_bounds__(256) splitk_reduce_norm_kernel(GemmArgs a, Nor
 // the fragment reads of the waves of weight-row half 0 exactly once, so those
 // waves' A_j A_j^T diagonals are the rows' sums of squares; the row sums
 // meet in LDS and scale the tile rows in the epilogue.
-template <int BN, int BM, int STAGES, int MODE, int BK = 64, int KG = 1, int RMS = 0>
+template <int BN, int BM, int STAGES, int MODE, int BK = 64, int KG = 1, int RMS = 0, bool EARLY = false>
 __global__ void __launch_bounds__(256 * KG)
 gemm_stage_kernel(GemmArgs a) {
   constexpr int NT = 256 * KG, NWV = 4 * KG;            // threads, waves
@@ -312,16 +312,14 @@ gemm_stage_kernel(GemmArgs a) {
   // this lane's row within a row group and its LDS slot; the slot holds
   // logical chunk (slot ^ swz(row)) of the row
   const int lrow = lane / CPR, slot = lane % CPR;
-  // EARLY (128 x 128 tiles): a stage is requested again as soon as its
-  // fragments are in registers, ahead of the products, so that two K-steps of
-  // loads are in flight and a wave waits for loads requested a whole K-step
-  // earlier; rows past the operands read their last row (what they compute is
-  // not stored), so that a load is one addition to an offset formed here. The
-  // smaller tiles (short products, more blocks a CU) lose 1-3 % by the longer
-  // start and the second barrier. ViT products of 9216 rows, 768 wide: VLM
-  // stage of the SmolVLA-shaped model with its vision encoder at batch 3 797
-  // -> 769 us.
-  constexpr bool EARLY = BN == 128 && BM == 128 && STAGES == 2 && KG == 1;
+  // EARLY (128 x 128 tiles, early_ok below): a stage is requested again as
+  // soon as its fragments are in registers, ahead of the products, so that two
+  // K-steps of loads are in flight and a wave waits for loads requested a
+  // whole K-step earlier; rows past the operands read their last row (what
+  // they compute is not stored), so that a load is one addition to an offset
+  // formed here. The smaller tiles (short products, more blocks a CU) lose
+  // 1-3 % by the longer start and the second barrier.
+  static_assert(!EARLY || (STAGES == 2 && KG == 1), "early requests: two stages, one wave group");
   constexpr int AHEAD = EARLY ? 2 : STAGES - 1;         // stages requested ahead
   const bool ktail = (K - kbeg) % BK != 0;
   long off[EARLY ? LOADS : 1];
@@ -774,8 +772,25 @@ static void launch_reduce(const GemmArgs& a, const NormArgs* fuse, hipStream_t s
   hipLaunchKernelGGL(splitk_reduce_kernel<MODE>, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, s, a);
 }
 
-template <int BN, int BM, int MODE>
-static void launch_staged(const GemmArgs& a0, const GemmPlan& p, const NormArgs* fuse, hipStream_t s) {
+// Early requests on 128 x 128 tiles. Rows of whole 128-byte lines: for the
+// residual and QKV epilogues (VLM stage of the SmolVLA-shaped model with its
+// vision encoder at batch 3, 9216 rows of 768: 738 us without, 725 with them
+// for the residual products, 709 with all); stores, GeGLU and K ranges are
+// 1-3 % slower with them (198 products; the GeGLU of the SmolVLA-shaped VLM
+// stage at batch 4, 231 us with, 226 without). A row that ends inside a line
+// shares that line between two K-steps: with the later step requested early
+// and fewer than two blocks a CU the line is fetched twice (342 blocks, K =
+// 6648, 106 us without, 133 with; 90 such products of K > 1152 9 % slower on
+// average, up to 30), with more blocks early requests win (42 products of over
+// 512 blocks 6 % faster on average, up to 15; 2706 x 3168 x 5136 173 without,
+// 154 with).
+static bool early_ok(const GemmArgs& a, const GemmPlan& p) {
+  if (a.lda % 64 == 0 && a.ldw % 64 == 0) return p.splits == 1 && (a.mode == EPI_RESID || a.mode == EPI_QKV);
+  return (long)((a.M + p.bm - 1) / p.bm) * ((a.N + p.bn - 1) / p.bn) * p.splits > 512;
+}
+
+template <int BN, int BM, int MODE, bool EARLY>
+static void launch_staged_as(const GemmArgs& a0, const GemmPlan& p, const NormArgs* fuse, hipStream_t s) {
   GemmArgs a = a0;
   a.epi_reg = 0;
   a.ksplit = p.ksplit;
@@ -783,18 +798,29 @@ static void launch_staged(const GemmArgs& a0, const GemmPlan& p, const NormArgs*
   dim3 grid((a.M + BM - 1) / BM, (a.N + BN - 1) / BN, a.splits);
   if (a.splits > 1) {
     // partial pass without epilogue, then the ordered reduce applies it
-    hipLaunchKernelGGL((gemm_stage_kernel<BN, BM, 2, EPI_STORE>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((gemm_stage_kernel<BN, BM, 2, EPI_STORE, 64, 1, 0, EARLY>), grid, dim3(256), 0, s, a);
     launch_reduce<MODE>(a, fuse, s);
     return;
   }
   a.epi_reg = BN == 128 && reg_epi_ok(a) ? 1 : 0;
   if constexpr (MODE == EPI_STORE || MODE == EPI_QKV || MODE == EPI_GEGLU || MODE == EPI_EULER) {
     if (a.rms_in) {
-      hipLaunchKernelGGL((gemm_stage_kernel<BN, BM, 2, MODE, 64, 1, 1>), grid, dim3(256), 0, s, a);
+      hipLaunchKernelGGL((gemm_stage_kernel<BN, BM, 2, MODE, 64, 1, 1, EARLY>), grid, dim3(256), 0, s, a);
       return;
     }
   }
-  hipLaunchKernelGGL((gemm_stage_kernel<BN, BM, 2, MODE>), grid, dim3(256), 0, s, a);
+  hipLaunchKernelGGL((gemm_stage_kernel<BN, BM, 2, MODE, 64, 1, 0, EARLY>), grid, dim3(256), 0, s, a);
+}
+
+template <int BN, int BM, int MODE>
+static void launch_staged(const GemmArgs& a, const GemmPlan& p, const NormArgs* fuse, hipStream_t s) {
+  if constexpr (BN == 128 && BM == 128) {
+    if (early_ok(a, p)) {
+      launch_staged_as<BN, BM, MODE, true>(a, p, fuse, s);
+      return;
+    }
+  }
+  launch_staged_as<BN, BM, MODE, false>(a, p, fuse, s);
 }
 
 template <int BT, int ST, int MODE>
