@@ -116,6 +116,17 @@ vla_status vla_debug_attention(int B, int Hq, int Hkv, int Lq, int hd, int et, c
                                hipStream_t stream);
 
 /*
+ * The launch plan of such an attention (with the workspace of a model's
+ * stage). Host only, as vla_debug_gemm_plan.
+ *  plan: int[6] = kernel (0 register-staged, 1 direct loads, 2 waves split the
+ *  keys, 3 fp32), head dim that rows are padded to, dims of it that a block
+ *  computes, groups of four waves that split a block's keys, key ranges over
+ *  blocks, keys per range.
+ * Status 1 (VLA_EINVAL) on bad arguments.
+ */
+vla_status vla_debug_attention_plan(int B, int Hq, int Hkv, int Lq, int hd, int et, int len0, int len1, int* plan);
+
+/*
  * Launch `blocks` one-wave workgroups on the pool stream restricted to
  * `cu_count` compute units (the VLM-side mask of vla_step, or the action-side
  * mask counted from the top when from_top != 0). Each workgroup sleeps

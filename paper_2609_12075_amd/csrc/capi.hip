@@ -213,6 +213,22 @@ unsigned char* scratch_ptr() {
 }  // namespace
 
 // ---------------------------------------------------------------- model API
+// the checked shape and contiguous layout of a test attention (no buffers)
+static AttnArgs attn_args(int B, int Hq, int Hkv, int Lq, int hd, int et, int len0, int len1) {
+  VLA_REQUIRE(B >= 1 && Hq >= 1 && Hkv >= 1 && Hq % Hkv == 0 && Lq >= 1, "bad attention shape");
+  VLA_REQUIRE(hd >= 8 && hd <= 256 && hd % 8 == 0, "hd must be a multiple of 8 in [8, 256]");
+  VLA_REQUIRE(len0 >= 1 && len1 >= 0, "segment 0 needs a key");
+  VLA_REQUIRE(et == ET_F32 || et == ET_BF16, "bad element type");
+  AttnArgs a{};
+  a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.Lq = Lq; a.hd = hd; a.et = et; a.scale = 1.0f / sqrtf((float)hd);
+  a.q_sb = (long)Hq * Lq * hd; a.q_sh = (long)Lq * hd; a.q_si = hd;
+  a.seg[0] = AttnSeg{nullptr, (long)Hkv * len0 * hd, (long)len0 * hd, hd, nullptr, (long)Hkv * len0 * hd, (long)len0 * hd, hd, len0};
+  a.seg[1] = AttnSeg{nullptr, (long)Hkv * len1 * hd, (long)len1 * hd, hd, nullptr, (long)Hkv * len1 * hd, (long)len1 * hd, hd, len1};
+  a.o_sb = (long)Lq * Hq * hd; a.o_sh = hd; a.o_si = (long)Hq * hd;   // [B][Lq][Hq*hd]
+  a.ws_floats = vla_model_s::kAttnFloats;
+  return a;
+}
+
 extern "C" {
 
 size_t vla_weight_count(const vla_config* cfg) {
@@ -531,21 +547,26 @@ vla_status vla_debug_attention(int B, int Hq, int Hkv, int Lq, int hd, int et, c
                                const void* v0, int len0, const void* k1, const void* v1, int len1, void* o,
                                hipStream_t s) {
   return guarded([&] {
-    VLA_REQUIRE(B >= 1 && Hq >= 1 && Hkv >= 1 && Hq % Hkv == 0 && Lq >= 1, "bad attention shape");
-    VLA_REQUIRE(hd >= 8 && hd <= 256 && hd % 8 == 0, "hd must be a multiple of 8 in [8, 256]");
-    VLA_REQUIRE(len0 >= 1 && len1 >= 0, "segment 0 needs a key");
+    AttnArgs a = attn_args(B, Hq, Hkv, Lq, hd, et, len0, len1);
     VLA_REQUIRE(q && k0 && v0 && o && (len1 == 0 || (k1 && v1)), "null attention buffer");
-    VLA_REQUIRE(et == ET_F32 || et == ET_BF16, "bad element type");
-    AttnArgs a{};
-    a.B = B; a.Hq = Hq; a.Hkv = Hkv; a.Lq = Lq; a.hd = hd; a.et = et; a.scale = 1.0f / sqrtf((float)hd);
-    a.q = q; a.q_sb = (long)Hq * Lq * hd; a.q_sh = (long)Lq * hd; a.q_si = hd;
-    a.seg[0] = AttnSeg{k0, (long)Hkv * len0 * hd, (long)len0 * hd, hd, v0, (long)Hkv * len0 * hd, (long)len0 * hd, hd, len0};
-    a.seg[1] = AttnSeg{k1, (long)Hkv * len1 * hd, (long)len1 * hd, hd, v1, (long)Hkv * len1 * hd, (long)len1 * hd, hd, len1};
-    a.o = o; a.o_sb = (long)Lq * Hq * hd; a.o_sh = hd; a.o_si = (long)Hq * hd;   // [B][Lq][Hq*hd]
-    a.ws = debug_ws(1, vla_model_s::kAttnFloats); a.ws_floats = vla_model_s::kAttnFloats;
+    a.q = q; a.o = o;
+    a.seg[0].k = k0; a.seg[0].v = v0; a.seg[1].k = k1; a.seg[1].v = v1;
+    a.ws = debug_ws(1, vla_model_s::kAttnFloats);
     a.zeros = debug_ws(2, 64);
     launch_attention(a, s);
     VLA_HIP(hipGetLastError());
+  });
+}
+
+vla_status vla_debug_attention_plan(int B, int Hq, int Hkv, int Lq, int hd, int et, int len0, int len1, int* plan) {
+  return guarded([&] {
+    AttnArgs a = attn_args(B, Hq, Hkv, Lq, hd, et, len0, len1);
+    VLA_REQUIRE(plan, "null plan");
+    // planning only: the addresses stand for a workspace and a zero buffer
+    a.ws = reinterpret_cast<float*>(uintptr_t{256});
+    a.zeros = a.ws;
+    const AttnPlan p = attn_plan(a);
+    plan[0] = p.kernel; plan[1] = p.hdp; plan[2] = p.dims; plan[3] = p.groups; plan[4] = p.splits; plan[5] = p.kchunk;
   });
 }
 

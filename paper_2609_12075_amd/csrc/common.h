@@ -187,6 +187,14 @@ struct AttnArgs {
 };
 void launch_attention(const AttnArgs& a, hipStream_t s);
 
+// Launch plan of an attention: the kernel, the head dim it pads rows to, the
+// dims that a block computes of it (fewer: blocks that share a row tile, or
+// subtiles past the head dim skipped), the groups of four waves that split a
+// block's keys, and the key ranges over blocks (kchunk keys each). Host only.
+enum AttnKernel { ATTN_STAGED = 0, ATTN_DIRECT = 1, ATTN_WAVE = 2, ATTN_F32 = 3 };
+struct AttnPlan { int kernel, hdp, dims, groups, splits, kchunk; };
+AttnPlan attn_plan(const AttnArgs& a);
+
 // Row normalisation of an fp32 [rows][d] stream into `out` (type out_type).
 // kind 0: RMSNorm * g;  kind 1: LayerNorm * g + b (g, b optional);
 // kind 2: LayerNorm * (1 + scale) + shift (adaLN modulation, vectors [d]).

@@ -1110,7 +1110,7 @@ __global__ void __launch_bounds__(64 * NW) attn_wave_kernel(AttnArgs a) {
 
 }  // namespace
 
-// Launch plan of a bf16 attention. Direct-load kernel: key groups inside a
+// Key groups and ranges of the kernels with blocks of 64 rows. Direct-load kernel: key groups inside a
 // block (KS = 2) whenever the grid leaves CUs without a second block (short
 // decode and small prefill grids), and key ranges over blocks (split-KV,
 // merged by attn_combine_kernel) only when the rounds of tiles they save
@@ -1119,7 +1119,7 @@ __global__ void __launch_bounds__(64 * NW) attn_wave_kernel(AttnArgs a) {
 // at 64, of 32 keys ~2.1 us at 256; the merge ~3.5 us), at most one block
 // per CU.
 // Register-staged kernel (head dim 72): split when fewer than 128 blocks.
-static void attn_plan(const AttnArgs& a, int& splits, int& kchunk, int& ks) {
+static void plan_ranges(const AttnArgs& a, int& splits, int& kchunk, int& ks) {
   const int rows = (a.Hq / a.Hkv) * a.Lq;
   const long blocks = (long)((rows + BQ - 1) / BQ) * a.Hkv * a.B;
   const int total = a.seg[0].len + a.seg[1].len, ntiles = (total + BKV - 1) / BKV;
@@ -1153,47 +1153,119 @@ static void attn_plan(const AttnArgs& a, int& splits, int& kchunk, int& ks) {
   splits = (ntiles + per - 1) / per;              // every range holds keys
 }
 
-// The kernel whose waves split the keys, where its blocks of 16 rows are few:
-// at most one a CU (head dims to 32: eight, whose 33 KiB of LDS share a CU;
-// over 128: two, one after the other), and up to 1024 keys (longer ranges:
-// split-KV over blocks). At head dim 256, two or four blocks share a row tile
-// where that leaves every CU at most one. Measured (us with the merge launch
-// of the other kernel; 290 keys, 5 KV heads of 64, 50 tokens: batch 1 and 4
-// 8.2 -> 5.5, batch 16, 800 blocks, 8.8 / 10.7; 866 keys, 1 KV head of 256,
-// 400 rows a request: batch 1 16.7 -> 10.0, 2 19.1 -> 10.6, 4 21.0 -> 13.4, 8
-// 25.5 -> 16.0; one request's prefill, 296 keys of 256 20.0 -> 9.5, 816 keys
-// 32.5 -> 25.4, batch 4 of the former, 592 blocks, 17.4 / 27; 296 keys of 32,
-// 17 rows, 32 heads: batch 3 7.7 -> 4.8, 32 15.0 -> 12.9; 256 keys of 72 8.8
-// -> 6.5, batch 3, 768 blocks, 9.2 / 15).
-static bool launch_wave(const AttnArgs& a, hipStream_t s) {
-  const int G = a.Hq / a.Hkv, keys = a.seg[0].len + a.seg[1].len;
-  const long tiles = ((long)G * a.Lq + 15) / 16, blocks = tiles * a.Hkv * a.B;
-  if (!a.zeros || keys > 1024 || blocks > (a.hd <= 32 ? 2048 : a.hd <= 128 ? 256 : 512)) return false;
-  const int ds = a.hd <= 128 || blocks * 2 > 256 ? 1 : blocks * 4 > 256 ? 2 : 4;
+// The kernel whose waves split the keys, where its blocks of 16 rows are few
+// and the keys at most 1024 (longer ranges: split-KV over blocks). At head dim
+// 256, two or four blocks share a row tile where that leaves every CU at most
+// one. Measured (us, the other kernel with its merge launch / this one):
+// - head dims 33 to 128, at most one block a CU: 290 keys, 5 KV heads of 64,
+//   50 tokens: batch 1 and 4 8.2 / 5.5; batch 16, 800 blocks, 8.8 / 10.7; 256
+//   keys of 72 8.8 / 6.5, batch 3, 768 blocks, 9.2 / 15.
+// - over 128, at most one a CU: 866 keys, 1 KV head of 256, 400 rows a
+//   request: batch 1 16.7 / 10.0, 2 19.1 / 10.6, 4 21.0 / 13.4, 8 25.5 / 16.0;
+//   one request's prefill, 296 keys of 256 20.0 / 9.5.
+// - 256, up to two a CU (one after the other), where the other kernel's blocks
+//   of 64 rows are well filled and its keys enough: 512 blocks of 128 rows a KV
+//   head, 160 keys 12.7 / 13.2, 200 keys (split there) 25.4 / 15.2, 800 keys
+//   31.7 / 26.3; 500 blocks of 400 rows, past the sizes it splits, 300 keys
+//   16.6 / 16.7, 800 29.2 / 24.8; 512 of 32 rows, 800 keys, 36.4 / 36.7. Head
+//   dims below 256 pay for the chunks past their end: 136, 400 blocks, 200
+//   keys 12.5 / 15.8.
+// - to 32, eight blocks a CU: by two lines (us) fitted to sweeps of 16-128
+//   rows a KV head, 32-1000 keys and 256-2048 blocks, within 10 %: this kernel
+//   by blocks a CU and keys (more than three blocks of eight waves start one
+//   after the other), the other by its blocks a CU and tiles of 64 keys. 1024
+//   blocks of 64 rows a KV head: 100 keys 5.2 / 6.3, 520 keys 10.5 / 9.7; of 17
+//   rows: 150 keys 7.0 / 6.8; 2048 of 16: 300 keys 24.0 / 16.1; of 64: 1000
+//   keys 21.7 / 22.9.
+static long row_blocks(const AttnArgs& a, int height) {
+  return ((long)(a.Hq / a.Hkv) * a.Lq + height - 1) / height * a.Hkv * a.B;
+}
+
+static bool wave_faster(const AttnArgs& a) {
+  const int keys = a.seg[0].len + a.seg[1].len;
+  const long blocks = row_blocks(a, 16), tall = row_blocks(a, BQ);    // of this kernel, of the other
+  if (!a.zeros || keys > 1024) return false;
+  if (a.hd > 32) {
+    if (blocks <= 256) return true;
+    return a.hd == 256 && blocks <= 512 && 3 * tall <= blocks && keys > (tall <= 128 ? 160 : 320);
+  }
+  if (blocks > 2048) return false;
+  const double w = std::max(1.0, blocks / 256.0), t = (double)((tall + 255) / 256);
+  const double t_wave = std::max(3.7 + 0.33 * w, 2.8 + 0.74 * w) + keys * (0.0012 + 0.0016 * w);
+  const double t_tall = 3.2 + 0.35 * t + (keys + BKV - 1) / BKV * (0.45 + 0.31 * t);
+  return t_wave <= t_tall;
+}
+
+AttnPlan attn_plan(const AttnArgs& a) {
+  AttnPlan p{};
+  p.splits = p.groups = 1;
+  if (a.et == ET_F32) {
+    p.kernel = ATTN_F32;
+    p.hdp = p.dims = a.hd <= 64 ? 64 : a.hd <= 128 ? 128 : 256;
+    return p;
+  }
+  if (wave_faster(a)) {
+    const long blocks = row_blocks(a, 16);
+    p.kernel = ATTN_WAVE;
+    p.hdp = a.hd <= 32 ? 32 : a.hd <= 64 ? 64 : a.hd <= 128 ? 128 : 256;
+    p.dims = p.hdp / (a.hd <= 128 || blocks * 2 > 256 ? 1 : blocks * 4 > 256 ? 2 : 4);
+    return p;
+  }
+  plan_ranges(a, p.splits, p.kchunk, p.groups);
+  // the direct-load kernel serves every head dim (a multiple of 8) with a
+  // zero buffer, padded to the next of 32, 64, 128, 256 (chunks past hd load
+  // zeros and are not stored): the ViT's 72 runs on the 128-wide variant
+  // (54.8 -> 33.4 us per pi0-shaped layer at batch 8 against the
+  // register-staged kernel padded to 96); callers without a zero buffer use
+  // the register-staged one
+  p.kernel = a.zeros ? ATTN_DIRECT : ATTN_STAGED;
+  if (a.zeros) {
+    p.hdp = a.hd <= 32 ? 32 : a.hd <= 64 ? 64 : a.hd <= 128 ? 128 : 256;
+    p.dims = p.hdp == 128 && a.hd <= 80 && p.groups == 1 ? 80 : p.hdp;
+  } else {
+    p.hdp = p.dims = a.hd <= 32 ? 32 : a.hd <= 64 ? 64 : a.hd <= 96 ? 96 : 256;
+  }
+  return p;
+}
+
+static void launch_wave(const AttnArgs& a, const AttnPlan& p, hipStream_t s) {
+  const int G = a.Hq / a.Hkv;
   AttnArgs b = a;
   b.splits = 1;
   b.G = G;
-  const dim3 grid((unsigned)tiles * ds, a.Hkv, a.B);
+  const dim3 grid((unsigned)((G * a.Lq + 15) / 16) * (p.hdp / p.dims), a.Hkv, a.B);
   // n / d = n mul >> 32 holds while n d < 2^32: at most 2048 blocks, of 16 rows
   auto mul = [](unsigned d) { return d == 1 ? 0u : (unsigned)(((1ull << 32) + d - 1) / d); };
   b.mul_x = mul(grid.x); b.mul_y = mul(grid.y); b.mul_q = mul(a.Lq);
 #define GO(H, V, N, K) hipLaunchKernelGGL((attn_wave_kernel<H, V, N, K>), grid, dim3(64 * N), 0, s, b)
-  if (a.hd <= 32) GO(32, 32, 8, 32);
-  else if (a.hd <= 64) GO(64, 64, 8, 32);
-  else if (a.hd <= 128) GO(128, 128, 8, 32);
-  else if (ds == 1) GO(256, 256, 8, 16);
-  else if (ds == 2) GO(256, 128, 8, 16);
+  if (p.hdp == 32) GO(32, 32, 8, 32);
+  else if (p.hdp == 64) GO(64, 64, 8, 32);
+  else if (p.hdp == 128) GO(128, 128, 8, 32);
+  else if (p.dims == 256) GO(256, 256, 8, 16);
+  else if (p.dims == 128) GO(256, 128, 8, 16);
   else GO(256, 64, 12, 16);
 #undef GO
-  return true;
+}
+
+template <int HDP, int KS, int HDU = HDP>
+static void launch_direct(const AttnArgs& b, hipStream_t s) {
+  const dim3 grid(((b.Hq / b.Hkv) * b.Lq + BQ - 1) / BQ, b.Hkv, b.B * b.splits);
+  hipLaunchKernelGGL((attn_v2_kernel<HDP, KS, HDU>), grid, dim3(256 * KS), 0, s, b);
+}
+
+template <int HDP>
+static void launch_reg_staged(const AttnArgs& b, hipStream_t s) {
+  const dim3 grid(((b.Hq / b.Hkv) * b.Lq + BQ - 1) / BQ, b.Hkv, b.B * b.splits);
+  hipLaunchKernelGGL(attn_mfma_kernel<HDP>, grid, dim3(256), 0, s, b);
 }
 
 void launch_attention(const AttnArgs& a, hipStream_t s) {
   if (a.B <= 0 || a.Lq <= 0) return;
-  if (a.et == ET_F32) {
+  const AttnPlan p = attn_plan(a);
+  if (p.kernel == ATTN_F32) {
     const dim3 grid(((a.Hq / a.Hkv) * a.Lq + 15) / 16, a.Hkv, a.B);
-    if (a.hd <= 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(512), 0, s, a);
-    else if (a.hd <= 128) hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(512), 0, s, a);
+    if (p.hdp == 64) hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(512), 0, s, a);
+    else if (p.hdp == 128) hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(512), 0, s, a);
     else hipLaunchKernelGGL(attn_f32_kernel<256>, grid, dim3(512), 0, s, a);
     return;
   }
@@ -1203,31 +1275,25 @@ void launch_attention(const AttnArgs& a, hipStream_t s) {
   for (const AttnSeg& sg : a.seg)
     VLA_REQUIRE(64L * 2 * std::max(std::labs(sg.k_si), std::labs(sg.v_si)) + 2L * a.hd < (1L << 32),
                 "attention key row stride too large");
-  if (launch_wave(a, s)) return;
+  if (p.kernel == ATTN_WAVE) {
+    launch_wave(a, p, s);
+    return;
+  }
   AttnArgs b = a;
-  int ks;
-  attn_plan(a, b.splits, b.kchunk, ks);
-  const int rows = (a.Hq / a.Hkv) * a.Lq;
-  dim3 grid((rows + BQ - 1) / BQ, a.Hkv, a.B * b.splits);
-  // the direct-load kernel serves every head dim (a multiple of 8) with a
-  // zero buffer, padded to the next of 32, 64, 128, 256 (chunks past hd load
-  // zeros and are not stored): the ViT's 72 runs on the 128-wide variant
-  // (54.8 -> 33.4 us per pi0-shaped layer at batch 8 against the
-  // register-staged kernel padded to 96); callers without a zero buffer use
-  // the register-staged one
-  const bool v2 = a.zeros != nullptr;
-  if (v2 && a.hd <= 32) hipLaunchKernelGGL((attn_v2_kernel<32, 1>), grid, dim3(256), 0, s, b);
-  else if (v2 && a.hd <= 64 && ks == 2) hipLaunchKernelGGL((attn_v2_kernel<64, 2>), grid, dim3(512), 0, s, b);
-  else if (v2 && a.hd <= 64) hipLaunchKernelGGL((attn_v2_kernel<64, 1>), grid, dim3(256), 0, s, b);
-  else if (v2 && a.hd <= 80 && ks == 1) hipLaunchKernelGGL((attn_v2_kernel<128, 1, 80>), grid, dim3(256), 0, s, b);
-  else if (v2 && a.hd <= 128 && ks == 2) hipLaunchKernelGGL((attn_v2_kernel<128, 2>), grid, dim3(512), 0, s, b);
-  else if (v2 && a.hd <= 128) hipLaunchKernelGGL((attn_v2_kernel<128, 1>), grid, dim3(256), 0, s, b);
-  else if (v2 && ks == 2) hipLaunchKernelGGL((attn_v2_kernel<256, 2>), grid, dim3(512), 0, s, b);
-  else if (v2) hipLaunchKernelGGL((attn_v2_kernel<256, 1>), grid, dim3(256), 0, s, b);
-  else if (a.hd <= 32) hipLaunchKernelGGL(attn_mfma_kernel<32>, grid, dim3(256), 0, s, b);
-  else if (a.hd <= 64) hipLaunchKernelGGL(attn_mfma_kernel<64>, grid, dim3(256), 0, s, b);
-  else if (a.hd <= 96) hipLaunchKernelGGL(attn_mfma_kernel<96>, grid, dim3(256), 0, s, b);
-  else hipLaunchKernelGGL(attn_mfma_kernel<256>, grid, dim3(256), 0, s, b);
+  b.splits = p.splits;
+  b.kchunk = p.kchunk;
+  if (p.kernel == ATTN_DIRECT) {
+    if (p.hdp == 32) launch_direct<32, 1>(b, s);
+    else if (p.hdp == 64) p.groups == 2 ? launch_direct<64, 2>(b, s) : launch_direct<64, 1>(b, s);
+    else if (p.dims == 80) launch_direct<128, 1, 80>(b, s);
+    else if (p.hdp == 128) p.groups == 2 ? launch_direct<128, 2>(b, s) : launch_direct<128, 1>(b, s);
+    else p.groups == 2 ? launch_direct<256, 2>(b, s) : launch_direct<256, 1>(b, s);
+  } else {
+    if (p.hdp == 32) launch_reg_staged<32>(b, s);
+    else if (p.hdp == 64) launch_reg_staged<64>(b, s);
+    else if (p.hdp == 96) launch_reg_staged<96>(b, s);
+    else launch_reg_staged<256>(b, s);
+  }
   if (b.splits > 1) {
     // 256-thread blocks of 4 wavefronts x 64 / LPR rows
     const long nrows = (long)a.B * a.Hq * a.Lq;

@@ -28,7 +28,7 @@ EXPORTS = ["vla_weight_count", "vla_create_model", "vla_destroy_model", "vla_set
            "vla_prefill", "vla_prefill_ex", "vla_denoise", "vla_step", "vla_last_error", "vla_shutdown",
            "vla_debug_gemm", "vla_debug_gemm_bf16", "vla_debug_resid_norm", "vla_debug_gemm_rms", "vla_debug_resid_copy", "vla_debug_attention",
            "vla_debug_cu_probe", "vla_debug_replay_gemm", "vla_gemm_noalloc", "vla_debug_sync_probe",
-           "vla_debug_gemm_plan"]
+           "vla_debug_gemm_plan", "vla_debug_attention_plan"]
 
 
 class VlaError(RuntimeError):
@@ -96,6 +96,8 @@ def lib():
         L.vla_debug_sync_probe.restype = ci
         L.vla_debug_gemm_plan.argtypes = [ci, ci, ci, ci, ci, ci, ci, ctypes.POINTER(ci)]
         L.vla_debug_gemm_plan.restype = ci
+        L.vla_debug_attention_plan.argtypes = [ci, ci, ci, ci, ci, ci, ci, ci, ctypes.POINTER(ci)]
+        L.vla_debug_attention_plan.restype = ci
         L.vla_debug_replay_gemm.argtypes = [vp, ci, ci, ci, vp, ctypes.POINTER(ctypes.c_double),
                                             ctypes.POINTER(ctypes.c_int)]
         L.vla_debug_replay_gemm.restype = ci
@@ -399,6 +401,15 @@ def debug_attention(q, k0, v0, k1=None, v1=None, stream=None):
     _check(lib().vla_debug_attention(B, Hq, Hkv, Lq, hd, et, _ptr(q), _ptr(k0), _ptr(v0), len0, _ptr(k1), _ptr(v1),
                                      len1, _ptr(o), _stream(stream)))
     return o
+
+
+def attention_plan(B, Hq, Hkv, Lq, hd, len0, len1=0, bf16=True):
+    """vla_debug_attention_plan: the launch plan of an attention (host only)."""
+    plan = (ctypes.c_int * 6)()
+    _check(lib().vla_debug_attention_plan(B, Hq, Hkv, Lq, hd, int(bool(bf16)), len0, len1, plan))
+    d = dict(zip(("kernel", "hdp", "dims", "groups", "splits", "kchunk"), list(plan)))
+    d["kernel"] = ("staged", "direct", "wave", "f32")[d["kernel"]]
+    return d
 
 
 def debug_sync_probe(kind: int, grid: int, iters: int, words: int = 0, spin_limit: int = 200000, buf=None, ctr=None,
