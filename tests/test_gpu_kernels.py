@@ -21,25 +21,23 @@ GEMM_SHAPES = [
     # (M, N, K): stage shapes and ragged edges
     (1, 16, 8), (17, 32, 592), (50, 720, 720), (130, 200, 64), (300, 1000, 264), (4, 6144, 1024),
     (800, 3840, 720), (3840, 960, 960), (240, 1600, 960), (37, 33, 40),
-    # multi-stage kernel tiles: 256x128 with a K tail, 128x128 with a K tail,
-    # 256x128 with ragged M, N and K
+    # LDS-staged 128 x 128 tiles: a K tail, two K ranges, ragged M, N and K
     (2048, 4096, 592), (2048, 2048, 4304), (4000, 5000, 200),
-    # small-M kernel: one and two weight-row subtiles, K tails, several K
-    # rounds, ragged N; 1024-1535 weight rows with K <= 1024 (ragged)
+    # up to 64 rows, the waves split K: 16 x 16, 32 x 16 and 32 x 32 tiles, K
+    # tails, several K rounds, ragged N
     (50, 3840, 720), (17, 1600, 1000), (63, 1537, 3000), (64, 8192, 1024), (17, 1024, 1024), (60, 1200, 1000),
-    # K ranges of the LDS-staged kernel (partial + ordered reduce), ragged
+    # more rows, the waves split K: 64 x 64 tiles, ragged; 32 x 16 and 32 x 32
     (800, 720, 1920), (600, 1000, 1544),
-    # register-pipelined 64 x 32 tiles with K ranges
     (100, 1024, 4096), (200, 720, 1920),
     # large-tile kernel (K >= 2048): 224-row tiles (2600 rows: 12 row tiles
     # fill one round as 11 of 256 rows would) with ragged M, N and K, and
     # 256-row tiles (3584 rows: 224-row tiles would need a second round)
     (2600, 4100, 2056), (3584, 4600, 2056),
-    # staged 64 x 64 tiles (short K, mid-sized M), ragged
-    (800, 1600, 720), (431, 2500, 1000),
-    # two wave groups per K-step of 128: 128 x 128 tiles, ragged M, N and K;
-    # 64 x 64 tiles with two and four K ranges (two and three stages), ragged
-    (777, 3000, 1000), (390, 1000, 4000), (130, 700, 1800), (300, 700, 1800),
+    # two wave groups per K-step of 128: 64 x 64 tiles, ragged; 128 x 128
+    # tiles, ragged M, N and K
+    (800, 1600, 720), (431, 2500, 1000), (777, 3000, 1000),
+    # the waves split K: 32 x 64, 32 x 16 and 32 x 32 tiles, ragged
+    (390, 1000, 4000), (130, 700, 1800), (300, 700, 1800),
     # a few hundred rows with K past 4096: LDS-staged tiles with K ranges
     # (the GR00T-like LLM MLP down and ViT MLP down at batch 1), ragged M
     (296, 2048, 16384), (256, 1152, 4304), (65, 1000, 8200),
@@ -97,7 +95,7 @@ def test_gemm_activations(act, amp):
     (16384, 3072, 768),
     # staged 128 x 128 and 128 x 64 tiles from registers, ragged N; through LDS
     (4000, 1616, 640), (1500, 1616, 640), (4000, 1608, 640),
-    # small-M kernel (LDS epilogue)
+    # few rows, the waves split K (LDS epilogue)
     (50, 8192, 1024),
 ])
 @pytest.mark.parametrize("glu,act", [(1, 0), (0, 2), (0, 0)])
@@ -113,7 +111,7 @@ def test_gemm_bf16_out(M, N, K, glu, act):
 @pytest.mark.parametrize("M,N,K,glu", [
     # folded RMSNorm: staged 128 x 64 tiles from registers (the action
     # stage's gate/up at batch 16), ragged N; 64 x 64 tiles with two wave
-    # groups and the small-M kernel through LDS
+    # groups and waves that split K through LDS
     (800, 3840, 720, 1), (1500, 1616, 640, 1), (1500, 1616, 640, 0), (400, 3840, 720, 1), (50, 3840, 720, 1),
 ])
 def test_gemm_bf16_out_rms(M, N, K, glu):
@@ -209,10 +207,9 @@ def test_resid_norm(M, N, K, kind):
 
 
 RMS_SHAPES = [
-    # small-M kernel, ragged; 64 x 64 tiles with three and two stages; 128 x 128
-    # tiles with two wave groups, ragged; 128 x 64 and 128 x 128 tiles with
-    # K-steps of 64; shapes whose unfolded plan would split K or take the
-    # register-pipelined or large-tile kernel
+    # waves that split K (32 x 32 and 16 x 16 tiles, ragged); 64 x 64 and 128 x
+    # 128 tiles with two wave groups, ragged; 128 x 64 and 128 x 128 tiles with
+    # K-steps of 64; waves again; a shape whose unfolded plan takes large tiles
     (50, 3840, 720), (17, 1600, 1000), (100, 1600, 720), (400, 3840, 720), (777, 3000, 1000),
     (800, 3840, 720), (1600, 3840, 720), (37, 33, 40), (200, 720, 1920), (2600, 4100, 2056),
 ]
@@ -242,8 +239,8 @@ def test_gemm_rms(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [
-    # register-pipelined kernel; 64 x 64 tiles with two wave groups (the
-    # residual update from registers); ragged, per-element epilogue
+    # waves that split K: 16 x 16, 64 x 64 and 32 x 32 tiles; ragged,
+    # per-element epilogue
     (50, 720, 1920), (800, 720, 1920), (800, 720, 960), (37, 33, 40), (130, 202, 64),
     # staged 128 x 64 and 128 x 128 tiles (LDS-staged update), ragged
     (3840, 960, 960), (2000, 1156, 1000), (4000, 1156, 640),
@@ -294,11 +291,11 @@ ATTN_SHAPES = [
     (2, 32, 32, 17, 32, 296, 0),     # DiT cross-attention
     (1, 4, 2, 7, 64, 5, 3),          # ragged, tiny
     (1, 2, 1, 1, 8, 1, 0),           # single key
-    # many blocks (one key group per block): prefill-sized grids
+    # many blocks: prefill-sized grids, blocks of 64 rows
     (8, 15, 5, 240, 64, 240, 0),
     (24, 8, 1, 100, 256, 150, 7),
     (70, 4, 1, 64, 128, 70, 0),
-    # head dim 128 with key groups, two segments
+    # head dim 128, few row tiles, two segments
     (2, 4, 2, 40, 128, 200, 10),
 ]
 
