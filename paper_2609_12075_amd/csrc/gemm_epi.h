@@ -22,6 +22,7 @@ __device__ __forceinline__ void sumsq8(const bf16x8& v, float& s0, float& s1) {
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+struct __attribute__((packed, aligned(4))) f32x4u { f32x4 v; };      // four floats at any float's address
 
 // ---------------------------------------------------------------- epilogue
 __device__ __forceinline__ float act_apply(float x, int act) {
@@ -82,8 +83,8 @@ __device__ __forceinline__ void epilogue4(const GemmArgs& a, int m, int n0, floa
         }
       } else {
         float* o = reinterpret_cast<float*>(a.out) + row + n0;
-        if (nv == 4 && ((reinterpret_cast<uintptr_t>(o) & 15) == 0)) {
-          *reinterpret_cast<f32x4*>(o) = f32x4{r[0], r[1], r[2], r[3]};
+        if (nv == 4) {
+          reinterpret_cast<f32x4u*>(o)->v = f32x4{r[0], r[1], r[2], r[3]};
         } else {
           for (int j = 0; j < nv; ++j) o[j] = r[j];
         }

@@ -5,12 +5,15 @@
 
 // The kernels whose waves split K (k_gemm_wave.hip): the tile (weight rows x
 // activation rows) and ring slots per wave for a product, NONE when another
-// kernel serves it better. Host only.
+// kernel serves it better; gather: rows the direct loads cannot take, loaded
+// into registers (no slots). Host only.
 struct WavePlan {
-  enum Tile { NONE, T16x16, T32x16, T32x32, T32x64, T64x64, GATHER } tile = NONE;
+  enum Tile { NONE, T16x16, T32x16, T32x32, T32x64, T64x64, T64x32, T16x64 } tile = NONE;
+  bool gather = false;
   int slots = 2;
+  int nw = 0;                      // waves that split K (0: as the tile has it)
   int bn() const;
-  int bm(int w_type) const;
+  int bm() const;
   int waves() const;
 };
 WavePlan wave_plan(const GemmArgs& a);

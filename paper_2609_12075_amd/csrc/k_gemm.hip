@@ -582,7 +582,7 @@ static GemmPlan plan_base(const GemmArgs& a) {
     const WavePlan w = wave_plan(a);
     if (w.tile != WavePlan::NONE) {
       p.kind = a.M <= 64 || a.rms_in ? 2 : 0;
-      p.bn = w.bn(); p.bm = w.bm(a.w_type); p.kg = w.waves(); p.stages = w.slots;
+      p.bn = w.bn(); p.bm = w.bm(); p.kg = w.waves(); p.stages = w.slots;
       p.ksplit = nk * BK;
       return p;
     }

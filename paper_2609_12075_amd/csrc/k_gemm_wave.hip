@@ -114,6 +114,34 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& a, f32x4 (&acc)[TN][
   }
 }
 
+// The end of a tile that one wave computes alone: the epilogue runs from the
+// accumulators, four columns of TM rows at a time.
+template <int TN, int TM, int MODE>
+__device__ __forceinline__ void finish_alone(const GemmArgs& a, const f32x4 (&acc)[TN][TM], int m0, int n0) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+  int ms[TM];
+  bool ok[TM];
+#pragma unroll
+  for (int j = 0; j < TM; ++j) {
+    ms[j] = m0 + 16 * j + lr;
+    ok[j] = ms[j] < a.M;
+  }
+#pragma unroll
+  for (int i = 0; i < TN; ++i) {
+    const int n = n0 + 16 * i + 4 * lq;
+    if (n >= a.N) continue;
+    if (a.epi_vec) {
+      epi_rows<MODE, TM>(a, acc[i], ms, ok, n);
+      continue;
+    }
+#pragma unroll
+    for (int j = 0; j < TM; ++j) {
+      float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+      epilogue4<MODE>(a, ms[j], n, v);
+    }
+  }
+}
+
 // The rows of this thread in the vector epilogue; true when it has any.
 template <int TN, int TM, int NW>
 __device__ __forceinline__ bool my_rows(const GemmArgs& a, int m0, int n0, int (&ms)[Tile<TN, TM, NW>::NIT],
@@ -252,13 +280,16 @@ __global__ void __launch_bounds__(64 * NW) gemm_wave_kernel(GemmArgs a) {
 // 64-byte pieces of K in flight per wave: for rows that the direct loads
 // cannot take. bf16: operands whose base is not 16-byte aligned (K and the
 // strides are multiples of 8). fp32: rows whose length, stride or base is no
-// multiple of 16 bytes, read element by element.
+// multiple of 16 bytes; the pieces around the end of K are read element by
+// element.
 template <typename T, int TN, int TM, int NW, int U, int MODE, int RMS>
 __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   using G = Tile<TN, TM, NW>;
   constexpr int E = 16 / sizeof(T), CK = 4 * E;
-  __shared__ __attribute__((aligned(16))) float red[NW * G::PLANE];
-  __shared__ float rsq[RMS ? NW * G::BM : 1];
+  constexpr bool ALONE = NW == 1;
+  static_assert(!ALONE || !RMS, "the row scales are formed with the waves' sums");
+  __shared__ __attribute__((aligned(16))) float red[ALONE ? 1 : NW * G::PLANE];
+  __shared__ float rsq[RMS && !ALONE ? NW * G::BM : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int bx, by, bz;
   xcd_remap_grouped(bx, by, bz, 8);
@@ -267,7 +298,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   const int lr = lane & 15, lk = (lane >> 4) * E;
   int ms[G::NIT];
   bool ok[G::NIT];
-  const bool fin = my_rows<TN, TM, NW>(a, m0, n0, ms, ok);
+  const bool fin = !ALONE && my_rows<TN, TM, NW>(a, m0, n0, ms, ok);
   EpiRows<MODE, G::NIT> epi;
   if (fin) epi.load(a, ms, ok, n0 + (tid % G::CPT) * 4);
   const T *wrow[TN], *arow[TM];
@@ -275,12 +306,13 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   for (int i = 0; i < TN; ++i) wrow[i] = reinterpret_cast<const T*>(a.W) + (long)min(n0 + i * 16 + lr, a.N - 1) * a.ldw;
 #pragma unroll
   for (int j = 0; j < TM; ++j) arow[j] = reinterpret_cast<const T*>(a.A) + (long)min(m0 + j * 16 + lr, a.M - 1) * a.lda;
-  // the lane's E elements from k on, zeros past K
-  auto frag = [&](const T* row, int k) {
+  // the lane's E elements from k on, zeros past K (whole: none is)
+  struct __attribute__((packed, aligned(sizeof(T)))) P { u32x4 v; };
+  auto frag = [&](const T* row, int k, bool whole) {
     if constexpr (sizeof(T) == 2) {
-      struct __attribute__((packed, aligned(2))) P { u32x4 v; };
       return k < K ? reinterpret_cast<const P*>(row + k)->v : u32x4{0, 0, 0, 0};
     } else {
+      if (whole) return reinterpret_cast<const P*>(row + k)->v;
       f32x4 v;
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = k + e < K ? (float)row[k + e] : 0.f;
@@ -298,14 +330,18 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   const int nch = (K + CK - 1) / CK;
   for (int c0 = wave; c0 < nch; c0 += NW * U) {
     u32x4 wf[U][TN], af[U][TM];
+    auto load = [&](bool whole) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = (c0 + u * NW) * CK + lk;
+      for (int u = 0; u < U; ++u) {
+        const int k = (c0 + u * NW) * CK + lk;
 #pragma unroll
-      for (int i = 0; i < TN; ++i) wf[u][i] = frag(wrow[i], k);
+        for (int i = 0; i < TN; ++i) wf[u][i] = frag(wrow[i], k, whole);
 #pragma unroll
-      for (int j = 0; j < TM; ++j) af[u][j] = frag(arow[j], k);
-    }
+        for (int j = 0; j < TM; ++j) af[u][j] = frag(arow[j], k, whole);
+      }
+    };
+    if (sizeof(T) == 4 && (c0 + (U - 1) * NW + 1) * CK <= K) load(true);
+    else load(false);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if constexpr (RMS) {
@@ -320,7 +356,8 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   }
 #pragma unroll
   for (int j = 0; j < TM; ++j) rs[j] += rs2[j];
-  finish_tile<TN, TM, NW, MODE, RMS>(a, acc, rs, red, rsq, epi, ms, ok, fin, m0, n0, wave);
+  if constexpr (ALONE) finish_alone<TN, TM, MODE>(a, acc, m0, n0);
+  else finish_tile<TN, TM, NW, MODE, RMS>(a, acc, rs, red, rsq, epi, ms, ok, fin, m0, n0, wave);
 }
 
 // ---------------------------------------------------------------- dispatch
@@ -336,20 +373,35 @@ void go(const GemmArgs& a, hipStream_t s) {
   hipLaunchKernelGGL((gemm_wave_kernel<T, TN, TM, NW, S, MODE, RMS>), (grid_of<TN, TM>(a)), dim3(64 * NW), 0, s, a);
 }
 
+template <typename T, int TN, int TM, int NW, int U, int MODE, int RMS>
+void go_gather(const GemmArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((gemm_gather_kernel<T, TN, TM, NW, U, MODE, RMS>), (grid_of<TN, TM>(a)), dim3(64 * NW), 0, s, a);
+}
+
 template <typename T, int MODE, int RMS>
 void launch(const GemmArgs& a, const WavePlan& p, hipStream_t s) {
+  if (p.gather) {
+    if constexpr (sizeof(T) == 2) {
+      go_gather<T, 1, 4, 8, 4, MODE, RMS>(a, s);
+    } else if constexpr (RMS) {
+      // (model widths are multiples of four)
+      throw VlaError{4, "a folded RMSNorm of fp32 rows needs rows of whole 16 bytes"};
+    } else {
+      if (p.tile == WavePlan::T16x16) go_gather<T, 1, 1, 8, 4, MODE, 0>(a, s);
+      else if (p.tile == WavePlan::T64x64) go_gather<T, 4, 4, 4, 2, MODE, 0>(a, s);
+      else if (p.tile == WavePlan::T64x32) go_gather<T, 4, 2, 1, 1, MODE, 0>(a, s);
+      else if (p.nw == 1) go_gather<T, 2, 2, 1, 2, MODE, 0>(a, s);
+      else go_gather<T, 2, 2, 4, 4, MODE, 0>(a, s);
+    }
+    return;
+  }
   switch (p.tile) {
     case WavePlan::T16x16: go<T, 1, 1, 8, 2, MODE, RMS>(a, s); break;
     case WavePlan::T32x16: go<T, 2, 1, 4, 2, MODE, RMS>(a, s); break;
     case WavePlan::T32x32: p.slots == 1 ? go<T, 2, 2, 4, 1, MODE, RMS>(a, s) : go<T, 2, 2, 4, 2, MODE, RMS>(a, s); break;
     case WavePlan::T32x64: go<T, 2, 4, 4, 2, MODE, RMS>(a, s); break;
     case WavePlan::T64x64: go<T, 4, 4, 4, 2, MODE, RMS>(a, s); break;
-    case WavePlan::GATHER:
-      if constexpr (sizeof(T) == 2)
-        hipLaunchKernelGGL((gemm_gather_kernel<T, 1, 4, 8, 4, MODE, RMS>), (grid_of<1, 4>(a)), dim3(512), 0, s, a);
-      else
-        hipLaunchKernelGGL((gemm_gather_kernel<T, 1, 1, 8, 4, MODE, RMS>), (grid_of<1, 1>(a)), dim3(512), 0, s, a);
-      break;
+    case WavePlan::T64x32: case WavePlan::T16x64:        // (gather only)
     case WavePlan::NONE: break;
   }
 }
@@ -370,26 +422,54 @@ void launch_mode(const GemmArgs& a, const WavePlan& p, hipStream_t s) {
 
 }  // namespace
 
-int WavePlan::bn() const { return tile == T16x16 || tile == GATHER ? 16 : tile == T64x64 ? 64 : 32; }
-int WavePlan::bm(int w_type) const {
-  if (tile == GATHER) return w_type == ET_BF16 ? 64 : 16;
-  return tile == T32x32 ? 32 : tile == T32x64 || tile == T64x64 ? 64 : 16;
+int WavePlan::bn() const { return tile == T16x16 || tile == T16x64 ? 16 : tile == T64x32 || tile == T64x64 ? 64 : 32; }
+int WavePlan::bm() const {
+  return tile == T16x16 || tile == T32x16 ? 16 : tile == T32x32 || tile == T64x32 ? 32 : 64;
 }
-int WavePlan::waves() const { return tile == T16x16 || tile == GATHER ? 8 : 4; }
+int WavePlan::waves() const { return nw ? nw : tile == T16x16 || tile == T16x64 ? 8 : 4; }
+
+// The tile of an fp32 product whose rows the direct loads cannot take. Few
+// output tiles: the waves of a block split K, as below. Many: 64 x 64 tiles
+// split K while they fit the CUs and K is long; otherwise each wave computes a
+// tile alone (there are waves enough, and a short K is no work to share), 32 x
+// 32 or, past five waves a CU, 64 x 32 (fewer reads of an operand row).
+// Measured (us; tiles by the number of waves that split K):
+//   rows x columns x K   16 x 16/8  32 x 32/4  64 x 64/4  32 x 32/1  64 x 32/1
+//   512 x 250 x 501          6.8        8.1       16.6       14.7       29.4
+//   1024 x 250 x 501        12.5        8.4       16.8       14.9       29.4
+//   1024 x 1000 x 65        18.5       12.1        8.6        7.2        9.1
+//   1024 x 1000 x 501       31.2       30.3       16.5       16.6       26.9
+//   1024 x 1000 x 2047       116         95         46         64        119
+//   2048 x 2048 x 65          64         36         26         18         16
+//   2048 x 2048 x 1021       200        212        143        132         96
+// (the vector unit's kernel that these replaced: 59, 59, 12.8, 59, 275, 18 and
+// 196; none of 700 shapes is over 1.2 us slower than it).
+static WavePlan gather_plan_f32(const GemmArgs& a) {
+  auto blocks = [&](long bn, long bm) { return ((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
+  constexpr long CUS = 256;
+  WavePlan p;
+  p.gather = true;
+  p.slots = 0;
+  if (blocks(16, 16) <= 2 * CUS) p.tile = WavePlan::T16x16;
+  else if (blocks(32, 32) <= CUS) p.tile = WavePlan::T32x32;
+  else if (a.K > 512 && blocks(64, 64) <= CUS) p.tile = WavePlan::T64x64;
+  else p.tile = blocks(32, 32) <= 5 * CUS ? WavePlan::T32x32 : WavePlan::T64x32, p.nw = 1;
+  return p;
+}
 
 WavePlan wave_plan(const GemmArgs& a) {
   WavePlan p;
   const bool f32 = a.w_type == ET_F32;
   const int per16 = f32 ? 4 : 8;               // elements per 16 bytes
   const bool direct = a.zeros && al16(a.A) && al16(a.W) && a.K % per16 == 0 && a.lda % per16 == 0 && a.ldw % per16 == 0;
+  auto blocks = [&](long bn, long bm) { return ((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
+  constexpr long CUS = 256;
   if (!direct) {
-    // bf16: only what no other kernel takes in this state
-    if (f32 || (a.M <= 64 && a.zeros)) p.tile = WavePlan::GATHER;
+    if (f32) return gather_plan_f32(a);
+    if (a.M <= 64 && a.zeros) p.tile = WavePlan::T16x64, p.gather = true, p.slots = 0;      // (only what no other kernel takes)
     return p;
   }
-  auto blocks = [&](long bn, long bm) { return ((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
   const long row_bytes = (long)a.K * 16 / per16;
-  constexpr long CUS = 256;
   // The smallest tile whose blocks leave no CU a second one. Up to 2 KiB of K
   // per row a 32 x 32 tile takes one ring slot (32 KiB of LDS, so that blocks
   // share CUs) and serves up to 640 blocks. Beyond, the staged tiles that

@@ -152,3 +152,44 @@ def test_attention_routes(shape, plan):
     # sums add a few 2^-22 of the summed magnitudes
     bound = 2.0 ** -8 * 1.01 * (mag + ref.abs())
     assert ((got - ref).abs() <= bound).all(), float(((got - ref).abs() / bound).max())
+
+
+# fp32 products whose rows the direct loads cannot take: 16 x 16 and 32 x 32
+# tiles whose waves split K, 64 x 64 ones (long K), and tiles of one wave alone,
+# 32 x 32 and 64 x 32, each ragged, with K below, at and past a piece, and rows
+# of 4-byte alignment only
+@pytest.mark.parametrize("M,N,K", [(33, 50, 9), (270, 250, 70), (700, 300, 1021), (600, 610, 7), (530, 500, 33),
+                                   (610, 600, 130), (2000, 900, 1), (2010, 899, 30), (1500, 1300, 61)])
+def test_f32_rows_of_any_length(M, N, K):
+    import torch
+    from paper_2609_12075_amd import vla
+    log(f"[gather f32] M={M} N={N} K={K}")
+    A, W = RNG.standard_normal((M, K)).astype(np.float32), RNG.standard_normal((N, K)).astype(np.float32)
+    bias = RNG.standard_normal(N).astype(np.float32)
+    ref = A.astype(np.float64) @ W.astype(np.float64).T + bias
+
+    def off(a):              # the same matrix one float past an aligned address
+        flat = torch.zeros(a.size + 4, device="cuda")
+        flat[1:1 + a.size] = torch.from_numpy(a).cuda().flatten()
+        return flat[1:1 + a.size].view(a.shape)
+
+    out = vla.debug_gemm(torch.from_numpy(A).cuda(), torch.from_numpy(W).cuda(), bias=torch.from_numpy(bias).cuda())
+    out1 = vla.debug_gemm(off(A), off(W), bias=torch.from_numpy(bias).cuda())
+    torch.cuda.synchronize()
+    # each of the K products and sums rounds once: |error| <= K 2^-24 sum |a w|,
+    # in practice its square root; a few of those
+    bound = 4 * np.sqrt(K) * 2.0 ** -24 * (np.abs(A) @ np.abs(W).T + np.abs(bias)) + 1e-7
+    assert (np.abs(out.cpu().numpy() - ref) <= bound).all()
+    if K % 4:
+        assert torch.equal(out, out1)
+
+
+# the same products as residual updates: fp32 models with MLP widths that are
+# no multiple of four (64 x 64, 32 x 32 and 64 x 32 tiles in the LLM, 16 x 16 in
+# the action expert)
+@pytest.mark.parametrize("llm_d,llm_mlp,act_mlp", [(512, 1030, 129), (512, 510, 514), (1024, 130, 129)])
+def test_f32_models_with_odd_mlp_widths(llm_d, llm_mlp, act_mlp):
+    from paper_2609_12075_amd import synth
+    from tests.test_gpu_parity import check_parity
+    check_parity(synth.CONFIGS["tiny"].with_(name=f"tiny-{llm_d}-{llm_mlp}", llm_d=llm_d, llm_mlp=llm_mlp, act_mlp=act_mlp,
+                                             n_text=128, max_batch=8), 8)
