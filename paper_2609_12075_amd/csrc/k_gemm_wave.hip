@@ -116,8 +116,8 @@ __device__ __forceinline__ void finish_tile(const GemmArgs& a, f32x4 (&acc)[TN][
 
 // The end of a tile that one wave computes alone: the epilogue runs from the
 // accumulators, four columns of TM rows at a time.
-template <int TN, int TM, int MODE>
-__device__ __forceinline__ void finish_alone(const GemmArgs& a, const f32x4 (&acc)[TN][TM], int m0, int n0) {
+template <int TN, int TM, int MODE, int RMS>
+__device__ __forceinline__ void finish_alone(const GemmArgs& a, f32x4 (&acc)[TN][TM], float (&rs)[TM], int m0, int n0) {
   const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
   int ms[TM];
   bool ok[TM];
@@ -125,6 +125,14 @@ __device__ __forceinline__ void finish_alone(const GemmArgs& a, const f32x4 (&ac
   for (int j = 0; j < TM; ++j) {
     ms[j] = m0 + 16 * j + lr;
     ok[j] = ms[j] < a.M;
+    if constexpr (RMS) {
+      // (the four lanes of a row hold its squares between them)
+      rs[j] += __shfl_xor(rs[j], 16);
+      rs[j] += __shfl_xor(rs[j], 32);
+      const float sc = rsqrtf(rs[j] / (float)a.rms_in + a.rms_eps);
+#pragma unroll
+      for (int i = 0; i < TN; ++i) acc[i][j] = row_scale(acc[i][j], sc);
+    }
   }
 #pragma unroll
   for (int i = 0; i < TN; ++i) {
@@ -278,7 +286,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_wave_kernel(GemmArgs a) {
 // ---------------------------------------------------------------- rows of any alignment
 // The same product with the fragments loaded straight into registers, U
 // 64-byte pieces of K in flight per wave: for rows that the direct loads
-// cannot take. bf16: operands whose base is not 16-byte aligned (K and the
+// cannot take, and fp32 products of many tiles and short K. bf16: operands whose base is not 16-byte aligned (K and the
 // strides are multiples of 8). fp32: rows whose length, stride or base is no
 // multiple of 16 bytes; the pieces around the end of K are read element by
 // element.
@@ -287,7 +295,6 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   using G = Tile<TN, TM, NW>;
   constexpr int E = 16 / sizeof(T), CK = 4 * E;
   constexpr bool ALONE = NW == 1;
-  static_assert(!ALONE || !RMS, "the row scales are formed with the waves' sums");
   __shared__ __attribute__((aligned(16))) float red[ALONE ? 1 : NW * G::PLANE];
   __shared__ float rsq[RMS && !ALONE ? NW * G::BM : 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -312,7 +319,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
     if constexpr (sizeof(T) == 2) {
       return k < K ? reinterpret_cast<const P*>(row + k)->v : u32x4{0, 0, 0, 0};
     } else {
-      if (whole) return reinterpret_cast<const P*>(row + k)->v;
+      if (whole || k + 4 <= K) return reinterpret_cast<const P*>(row + k)->v;
       f32x4 v;
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = k + e < K ? (float)row[k + e] : 0.f;
@@ -356,7 +363,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   }
 #pragma unroll
   for (int j = 0; j < TM; ++j) rs[j] += rs2[j];
-  if constexpr (ALONE) finish_alone<TN, TM, MODE>(a, acc, m0, n0);
+  if constexpr (ALONE) finish_alone<TN, TM, MODE, RMS>(a, acc, rs, m0, n0);
   else finish_tile<TN, TM, NW, MODE, RMS>(a, acc, rs, red, rsq, epi, ms, ok, fin, m0, n0, wave);
 }
 
@@ -383,15 +390,12 @@ void launch(const GemmArgs& a, const WavePlan& p, hipStream_t s) {
   if (p.gather) {
     if constexpr (sizeof(T) == 2) {
       go_gather<T, 1, 4, 8, 4, MODE, RMS>(a, s);
-    } else if constexpr (RMS) {
-      // (model widths are multiples of four)
-      throw VlaError{4, "a folded RMSNorm of fp32 rows needs rows of whole 16 bytes"};
     } else {
-      if (p.tile == WavePlan::T16x16) go_gather<T, 1, 1, 8, 4, MODE, 0>(a, s);
-      else if (p.tile == WavePlan::T64x64) go_gather<T, 4, 4, 4, 2, MODE, 0>(a, s);
-      else if (p.tile == WavePlan::T64x32) go_gather<T, 4, 2, 1, 1, MODE, 0>(a, s);
-      else if (p.nw == 1) go_gather<T, 2, 2, 1, 2, MODE, 0>(a, s);
-      else go_gather<T, 2, 2, 4, 4, MODE, 0>(a, s);
+      if (p.tile == WavePlan::T16x16) go_gather<T, 1, 1, 8, 4, MODE, RMS>(a, s);
+      else if (p.tile == WavePlan::T64x64) go_gather<T, 4, 4, 4, 2, MODE, RMS>(a, s);
+      else if (p.tile == WavePlan::T64x32) go_gather<T, 4, 2, 1, 1, MODE, RMS>(a, s);
+      else if (p.nw == 1) go_gather<T, 2, 2, 1, 2, MODE, RMS>(a, s);
+      else go_gather<T, 2, 2, 4, 4, MODE, RMS>(a, s);
     }
     return;
   }
@@ -444,6 +448,12 @@ int WavePlan::waves() const { return nw ? nw : tile == T16x16 || tile == T16x64 
 //   2048 x 2048 x 1021       200        212        143        132         96
 // (the vector unit's kernel that these replaced: 59, 59, 12.8, 59, 275, 18 and
 // 196; none of 700 shapes is over 1.2 us slower than it).
+// Rows that the direct loads can take go this way too where K is so short that
+// filling 128 KiB of ring a CU is most of the time: past 640 tiles of 32 x 32,
+// K to 96, past five a CU to 128 (direct loads / this / the vector unit: 1024 x
+// 1000 x 64 7.1 / 6.1 / 10.8, x 128 7.5 / 8.0 / 17; 2048 x 2048 x 8 22 / 9 /
+// 9, x 64 22 / 16 / 16, x 128 23.1 / 19.4 / 24, x 256 32 / 30 / 42; 8000 x 1000 x
+// 128 42 / 36 / 40, x 256 60 / 60 / 75).
 static WavePlan gather_plan_f32(const GemmArgs& a) {
   auto blocks = [&](long bn, long bm) { return ((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
   constexpr long CUS = 256;
@@ -464,8 +474,9 @@ WavePlan wave_plan(const GemmArgs& a) {
   const bool direct = a.zeros && al16(a.A) && al16(a.W) && a.K % per16 == 0 && a.lda % per16 == 0 && a.ldw % per16 == 0;
   auto blocks = [&](long bn, long bm) { return ((a.N + bn - 1) / bn) * ((a.M + bm - 1) / bm); };
   constexpr long CUS = 256;
+  const long t32 = blocks(32, 32);
+  if (f32 && (!direct || (t32 > 640 && a.K <= (t32 > 5 * CUS ? 128 : 96)))) return gather_plan_f32(a);
   if (!direct) {
-    if (f32) return gather_plan_f32(a);
     if (a.M <= 64 && a.zeros) p.tile = WavePlan::T16x64, p.gather = true, p.slots = 0;      // (only what no other kernel takes)
     return p;
   }

@@ -193,3 +193,29 @@ def test_f32_models_with_odd_mlp_widths(llm_d, llm_mlp, act_mlp):
     from tests.test_gpu_parity import check_parity
     check_parity(synth.CONFIGS["tiny"].with_(name=f"tiny-{llm_d}-{llm_mlp}", llm_d=llm_d, llm_mlp=llm_mlp, act_mlp=act_mlp,
                                              n_text=128, max_batch=8), 8)
+
+
+# short K and many tiles: 32 x 32 and 64 x 32 tiles of one wave for aligned rows
+# too, as stores and (width of the action expert, batch) with the folded norm
+@pytest.mark.parametrize("M,N,K", [(830, 840, 4), (1000, 700, 96), (1500, 1300, 20), (2100, 900, 128)])
+def test_f32_short_k_many_tiles(M, N, K):
+    import torch
+    from paper_2609_12075_amd import vla
+    log(f"[alone f32] M={M} N={N} K={K}")
+    A, W = RNG.standard_normal((M, K)).astype(np.float32), RNG.standard_normal((N, K)).astype(np.float32)
+    out = vla.debug_gemm(torch.from_numpy(A).cuda(), torch.from_numpy(W).cuda())
+    bound = 4 * np.sqrt(K) * 2.0 ** -24 * (np.abs(A) @ np.abs(W).T) + 1e-7
+    assert (np.abs(out.cpu().numpy() - A.astype(np.float64) @ W.astype(np.float64).T) <= bound).all()
+
+
+@pytest.mark.parametrize("act_d,batch", [(64, 128), (96, 130), (128, 210)])
+def test_f32_folded_norms_of_short_rows(act_d, batch):
+    from oracle import vla as OV
+    from paper_2609_12075_amd import synth
+    from tests.gpu_util import check_chunk, oracle_params, run
+    cfg = synth.CONFIGS["tiny"].with_(name=f"tiny-a{act_d}-b{batch}", act_d=act_d, max_batch=batch)
+    inp = synth.make_inputs(cfg, batch)
+    act, _ = run(cfg, inp)
+    rows = [0, batch // 2, batch - 1]
+    ref, _ = OV.run(cfg, oracle_params(cfg), inp, rows=rows)
+    check_chunk(act[rows], ref, inp["noise"][rows], 1e-4, cfg.name)
