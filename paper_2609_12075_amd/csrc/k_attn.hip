@@ -336,6 +336,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnArgs a) {
 template <int HDP>
 __global__ void __launch_bounds__(512) attn_f32_kernel(AttnArgs a) {
   constexpr int NW = 8, NC = HDP / 16;               // 16-wide chunks of the head dimension
+  constexpr bool LATE = HDP > 128;                   // values after the scores (keys and values at once do not fit)
   constexpr int REC = HDP / 4 + 4;                   // merge record of a lane: output, max, sum, pad
   __shared__ __attribute__((aligned(16))) float mg[NW / 2][64 * REC];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -368,25 +369,21 @@ __global__ void __launch_bounds__(512) attn_f32_kernel(AttnArgs a) {
     f32x4 kf[NC], vf[NC];                            // vf[c][e]: V[key 4 lk + e][16 c + lr]
 #pragma unroll
     for (int c = 0; c < NC; ++c) kf[c] = c * 16 + lk * 4 < hd ? *reinterpret_cast<const f32x4*>(kp + c * 16 + lk * 4) : zero;
+    auto load_v = [&]() {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float* vp = row(min(t * 16 + lk * 4 + e, total - 1), true);
+      for (int e = 0; e < 4; ++e) {
+        const float* vp = row(min(t * 16 + lk * 4 + e, total - 1), true);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) vf[c][e] = c * 16 + lr < hd ? vp[c * 16 + lr] : 0.f;
-    }
-    // (probability 0 times an infinity of the last key would be a NaN)
-    if (t * 16 + 16 > total) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-          if (t * 16 + lk * 4 + e >= total) vf[c][e] = 0.f;
-    }
+        for (int c = 0; c < NC; ++c) vf[c][e] = c * 16 + lr < hd ? vp[c * 16 + lr] : 0.f;
+      }
+    };
+    if constexpr (!LATE) load_v();
     f32x4 sc = zero;
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
       for (int e = 0; e < 4; ++e) sc = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][e], qf[c][e], sc, 0, 0, 0);
+    if constexpr (LATE) load_v();
     float mx = -INFINITY;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -406,6 +403,14 @@ __global__ void __launch_bounds__(512) attn_f32_kernel(AttnArgs a) {
     ps += __shfl_xor(ps, 32);
     l_run = l_run * alpha + ps;
     m_run = m_new;
+    // (probability 0 times an infinity of the last key would be a NaN)
+    if (t * 16 + 16 > total) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          if (t * 16 + lk * 4 + e >= total) vf[c][e] = 0.f;
+    }
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       o[c] *= alpha;
