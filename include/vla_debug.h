@@ -173,9 +173,10 @@ vla_status vla_debug_sync_probe(int kind, int grid, int iters, int words, int sp
  *  plan: int[8] = weight rows and activation rows per tile, number of K
  *  ranges, K length per range, kernel kind (0 register-pipelined, or,
  *  where the last number is over 1, the waves of a block split K; 1
- *  LDS-staged; 2 the waves split K, few rows or a folded norm; 3 large-tile;
- *  4 LDS-staged with K-steps of 128), LDS stages, K-step length, wave groups
- *  sharing each K-step (kinds 1-4) or waves among which K is split.
+ *  LDS-staged; 2 the waves split K, few rows, a folded norm or fp32; 3
+ *  large-tile; 4 LDS-staged with K-steps of 128), LDS stages (0: rows that the
+ *  direct loads cannot take, gathered into registers), K-step length, wave
+ *  groups sharing each K-step or waves among which K is split.
  * Status 1 (VLA_EINVAL) on bad arguments.
  */
 vla_status vla_debug_gemm_plan(int M, int N, int K, int mode, int out_bf16, int rms, int norm_follows, int* plan);

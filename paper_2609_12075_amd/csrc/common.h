@@ -146,13 +146,14 @@ struct GemmArgs {
 
 void launch_gemm(const GemmArgs& a, hipStream_t s);
 
-// Launch plan of a bf16 projection: tile (bn weight rows x bm activation
-// rows), number of K ranges and the K length per range.
+// Launch plan of a projection: tile (bn weight rows x bm activation rows),
+// number of K ranges and the K length per range.
 // kind 0: register-pipelined, or with kg > 1 the waves of a block split K; 1:
 // multi-stage (K-steps of 64), 2: the waves split K, at most 64 activation
-// rows or a folded RMSNorm, 3: large-tile, 4: multi-stage 64 x 64 or 128 x 128
-// tiles with K-steps of 128 (stages 2 or 3); kg: wave groups sharing each
-// K-step (4 waves each), or the waves among which K is split
+// rows, a folded RMSNorm or fp32, 3: large-tile, 4: multi-stage 64 x 64 or 128
+// x 128 tiles with K-steps of 128 (stages 2 or 3); kg: wave groups sharing
+// each K-step (4 waves each), or the waves among which K is split (of which a
+// plan without stages gathers its fragments straight into registers)
 struct GemmPlan { int bn, bm, splits, ksplit, kind, stages = 2, bk = 64, kg = 1; };
 GemmPlan gemm_plan(const GemmArgs& a);
 

@@ -14,6 +14,7 @@ struct WavePlan {
   int nw = 0;                      // waves that split K (0: as the tile has it)
   int bn() const;
   int bm() const;
+  int k_step(int w_type) const;    // elements of K per chunk, or that a gathering wave has in flight
   int waves() const;
 };
 WavePlan wave_plan(const GemmArgs& a);

@@ -559,8 +559,12 @@ gemm_stage_kernel(GemmArgs a) {
 static GemmPlan plan_base(const GemmArgs& a) {
   constexpr int BK = 64;
   GemmPlan p{64, 32, 1, 64, 0};
+  auto take_wave = [&](const WavePlan& w, int kind) {
+    p.kind = kind;
+    p.bn = w.bn(); p.bm = w.bm(); p.kg = w.waves(); p.stages = w.slots; p.bk = w.k_step(a.w_type);
+  };
   if (a.w_type == ET_F32) {
-    p.bm = 64;
+    take_wave(wave_plan(a), 2);
     p.ksplit = a.K;
     return p;
   }
@@ -581,8 +585,7 @@ static GemmPlan plan_base(const GemmArgs& a) {
     // ranges; the rule and its measurements are wave_plan's)
     const WavePlan w = wave_plan(a);
     if (w.tile != WavePlan::NONE) {
-      p.kind = a.M <= 64 || a.rms_in ? 2 : 0;
-      p.bn = w.bn(); p.bm = w.bm(); p.kg = w.waves(); p.stages = w.slots;
+      take_wave(w, a.M <= 64 || a.rms_in ? 2 : 0);
       p.ksplit = nk * BK;
       return p;
     }
@@ -712,8 +715,8 @@ static GemmPlan plan_base(const GemmArgs& a) {
 }
 
 // A product with a folded RMSNorm needs each row's whole K in one block: the
-// plan without K ranges, on a kernel that sums the squares (LDS-staged or
-// small-M).
+// plan without K ranges, on a kernel that sums the squares (LDS-staged, or
+// with waves that split K).
 GemmPlan gemm_plan(const GemmArgs& a) {
   if (!a.rms_in || a.w_type != ET_BF16) return plan_base(a);
   GemmArgs b = a;
@@ -874,10 +877,6 @@ static void launch_mfma(const GemmArgs& a0, const GemmPlan& p, const NormArgs* f
 // passed when the plan splits K and the product is a residual projection)
 template <int MODE>
 static void launch_mode(const GemmArgs& a, const GemmPlan& p, const NormArgs* fuse, hipStream_t s) {
-  if (a.w_type == ET_F32) {
-    launch_gemm_wave(a, wave_plan(a), s);
-    return;
-  }
   if (p.kind == 3) {
     launch_gemm_big(a, p.bm, s);
     return;
@@ -944,7 +943,7 @@ void launch_gemm(const GemmArgs& a0, hipStream_t s) {
     throw VlaError{4, "a bf16 copy needs an fp32 store or residual epilogue without row groups"};
   GemmArgs a = a0;
   a.epi_vec = epi_vec_ok(a) ? 1 : 0;
-  const GemmPlan p = a.w_type == ET_F32 ? GemmPlan{} : gemm_plan(a);
+  const GemmPlan p = gemm_plan(a);
   switch (a.mode) {
     case EPI_STORE: launch_mode<EPI_STORE>(a, p, nullptr, s); break;
     case EPI_RESID: launch_mode<EPI_RESID>(a, p, nullptr, s); break;

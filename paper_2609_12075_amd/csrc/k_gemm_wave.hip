@@ -430,6 +430,10 @@ int WavePlan::bn() const { return tile == T16x16 || tile == T16x64 ? 16 : tile =
 int WavePlan::bm() const {
   return tile == T16x16 || tile == T32x16 ? 16 : tile == T32x32 || tile == T64x32 ? 32 : 64;
 }
+int WavePlan::k_step(int w_type) const {
+  const int e = w_type == ET_F32 ? 4 : 8;                  // elements of 16 bytes
+  return gather ? 4 * e * (tile == T64x32 ? 1 : tile == T64x64 || nw == 1 ? 2 : 4) : 8 * e;
+}
 int WavePlan::waves() const { return nw ? nw : tile == T16x16 || tile == T16x64 ? 8 : 4; }
 
 // The tile of an fp32 product whose rows the direct loads cannot take. Few

@@ -237,12 +237,13 @@ class Model:
 
     def replay_gemm(self, which: int, batch: int, iters: int, stream=None):
         """Enqueue `iters` launches of one stage projection. Returns (flops of
-        one launch, plan dict: tile_n, tile_m, splits, mode, kind, stages, bk, kg, rms)."""
+        one launch, plan dict: tile_n, tile_m, splits, mode, kind, stages, bk, kg, rms, f32)."""
         f = ctypes.c_double(0.0)
         plan = (ctypes.c_int * 9)()
         _check(lib().vla_debug_replay_gemm(self.handle, which, batch, iters, _stream(stream), ctypes.byref(f), plan))
         return f.value, {"tile_n": plan[0], "tile_m": plan[1], "splits": plan[2], "mode": plan[3], "kind": plan[4],
-                         "stages": plan[5], "bk": plan[6], "kg": plan[7], "rms": plan[8]}
+                         "stages": plan[5], "bk": plan[6], "kg": plan[7], "rms": plan[8],
+                         "f32": int(self.cfg.dtype == synth.DTYPE_F32)}
 
     @staticmethod
     def kernel_symbol(plan):
@@ -253,8 +254,11 @@ class Model:
             return (f"gemm_stage_kernelILi{plan['tile_n']}ELi{plan['tile_m']}ELi{plan['stages']}ELi{mode}"
                     f"ELi{plan['bk']}ELi{plan['kg']}ELi{plan['rms']}E")
         if plan["kind"] == 2 or (plan["kind"] == 0 and plan["kg"] > 1):
-            return (f"gemm_wave_kernelIDF16bLi{plan['tile_n'] // 16}ELi{plan['tile_m'] // 16}ELi{plan['kg']}"
-                    f"ELi{plan['stages']}ELi{mode}ELi{plan['rms']}E")
+            et, tile = "f" if plan["f32"] else "DF16b", f"Li{plan['tile_n'] // 16}ELi{plan['tile_m'] // 16}ELi{plan['kg']}E"
+            if plan["stages"] == 0:      # a piece is 64 bytes of K
+                pieces = plan["bk"] // (16 if plan["f32"] else 32)
+                return f"gemm_gather_kernelI{et}{tile}Li{pieces}ELi{mode}ELi{plan['rms']}E"
+            return f"gemm_wave_kernelI{et}{tile}Li{plan['stages']}ELi{mode}ELi{plan['rms']}E"
         if plan["kind"] == 3:
             return f"gemm_big_kernelILi{mode}ELi{plan['tile_m'] // 32}E"
         return f"gemm_mfma_kernelILi{plan['tile_n']}ELi{plan['tile_m']}EDF16bLi{mode}E"

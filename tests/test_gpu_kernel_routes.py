@@ -219,3 +219,22 @@ def test_f32_folded_norms_of_short_rows(act_d, batch):
     rows = [0, batch // 2, batch - 1]
     ref, _ = OV.run(cfg, oracle_params(cfg), inp, rows=rows)
     check_chunk(act[rows], ref, inp["noise"][rows], 1e-4, cfg.name)
+
+
+@pytest.mark.parametrize("kw,stages", [({}, 2), ({"act_mlp": 129, "llm_mlp": 514}, 0), ({"max_batch": 64}, 2)])
+def test_f32_plans_name_what_is_launched(kw, stages):
+    """A replay of an fp32 model's projections reports the tile and waves of
+    the kernel that it launches."""
+    from paper_2609_12075_amd import synth, vla
+    cfg = synth.CONFIGS["tiny"].with_(name="tiny-plans", **kw)
+    m = vla.Model(cfg, synth.make_weights(cfg))
+    with open(vla._LIB_PATH, "rb") as f:
+        names = f.read()
+    for which in range(4):
+        flops, p = m.replay_gemm(which, cfg.max_batch, 0)
+        where = (which, p, vla.Model.kernel_symbol(p))
+        assert p["f32"] == 1 and p["kind"] == 2 and p["splits"] == 1, where
+        assert vla.Model.kernel_symbol(p).encode() in names, where
+        assert p["tile_n"] in (16, 32, 64) and p["tile_m"] in (16, 32, 64) and p["kg"] in (1, 4, 8), where
+    assert m.replay_gemm(3, cfg.max_batch, 0)[1]["stages"] == stages          # the down projection: K = act_mlp
+    m.close()

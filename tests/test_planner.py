@@ -131,3 +131,17 @@ def test_attention_plan_invariants():
     assert vla.lib().vla_debug_attention_plan(1, 3, 2, 4, 64, 1, 8, 0, bad) == vla.VLA_EINVAL
     assert vla.lib().vla_debug_attention_plan(1, 2, 2, 4, 60, 1, 8, 0, bad) == vla.VLA_EINVAL
     assert vla.lib().vla_debug_attention_plan(1, 2, 2, 4, 64, 1, 0, 8, bad) == vla.VLA_EINVAL
+
+
+@pytest.mark.parametrize("mode,rms", [(STORE, False), (RESID, False), (GEGLU, True), (QKV, True), (EULER, True)])
+def test_plans_name_kernels_of_the_library(mode, rms):
+    """The kernel that a plan names (the profiler's name of it) is one that
+    the library holds; waves that split K are reported under two kinds."""
+    with open(vla._LIB_PATH, "rb") as f:
+        names = f.read()
+    for M, N, K in itertools.product([1, 50, 100, 300, 800, 3000, 7000], [16, 720, 1152, 2048, 8192], [64, 720, 2048, 4304, 8192]):
+        out_bf16 = mode in (GEGLU, QKV)
+        p = dict(plan(M, N, K, mode, out_bf16=out_bf16, rms=rms), mode=mode, rms=int(rms), f32=0)
+        assert vla.Model.kernel_symbol(p).encode() in names, (M, N, K, p, vla.Model.kernel_symbol(p))
+        if p["kind"] == 0 and p["kg"] > 1:
+            assert M > 64 and p["splits"] == 1 and p["ksplit"] >= K and p["stages"] in (1, 2), (M, N, K, p)
