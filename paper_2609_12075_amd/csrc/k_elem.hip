@@ -2,6 +2,8 @@
 // LayerNorm / adaLN modulation (one to four wavefronts per row, wave64 reductions),
 // patch extraction, token embedding, the flow-time sinusoid, RoPE tables,
 // parameter conversion and a placement probe for CU-masked streams.
+#include <algorithm>
+
 #include "common.h"
 #include "rownorm.h"
 
@@ -39,22 +41,24 @@ __global__ void __launch_bounds__(256) norm_kernel(NormArgs a) {
 // ---------------------------------------------------------------- staging
 // One thread per V neighbouring pixels of a row (one vector load; a patch row
 // is p pixels, V divides p and the image width, so they stay in one patch):
-// bpp blocks per (image, channel) plane cover its pixels in raster order, so
-// that reads are whole rows; the threads after the last pixel's fill the
-// columns past 3 p^2 (planes of channel 0 only). Bound by HBM: nine 512 x 512
+// a row of blocks per (image, channel) plane covers its pixels in raster order,
+// so that reads are whole rows; the threads after the last pixel's fill the
+// columns past 3 p^2 (planes of channel 0 only). The pixels are the caller's,
+// at any float's address. Bound by HBM: nine 512 x 512
 // images 41 us (a thread per output element, each of its reads a 64-byte
 // piece) -> 10 us.
 template <int V>
-__global__ void __launch_bounds__(256) im2col_kernel(const float* pix, int hw, int p, int bpp, void* out, int ldo, int out_type) {
+__global__ void __launch_bounds__(256) im2col_kernel(const float* pix, int hw, int p, void* out, int ldo, int out_type) {
   typedef __attribute__((ext_vector_type(V))) float fv;
+  struct __attribute__((packed, aligned(4))) fvu { fv v; };
   typedef __attribute__((ext_vector_type(V))) __bf16 bv;
   const int gp = hw / p, T = gp * gp, pp = p * p;
   const unsigned per_row = hw / V, pixels = per_row * hw;
-  const int plane = blockIdx.x / bpp, img = plane / 3, c = plane % 3;
-  const unsigned e = (blockIdx.x % bpp) * 256 + threadIdx.x;
+  const int plane = blockIdx.y, img = plane / 3, c = plane % 3;
+  const unsigned e = blockIdx.x * 256 + threadIdx.x;
   if (e < pixels) {
     const int y = (int)(e / per_row), x = (int)(e % per_row) * V;
-    const fv v = *reinterpret_cast<const fv*>(pix + ((long)plane * hw + y) * hw + x);
+    const fv v = reinterpret_cast<const fvu*>(pix + ((long)plane * hw + y) * hw + x)->v;
     const long o = ((long)img * T + (y / p) * gp + x / p) * ldo + c * pp + (y % p) * p + x % p;
     if (out_type == ET_BF16) {
       bv w;
@@ -264,11 +268,17 @@ void launch_norm(const NormArgs& a, hipStream_t s) {
 void launch_im2col(const float* pix, int n_images, int hw, int p, void* out, int ldo, int out_type, hipStream_t s) {
   const int V = p % 4 == 0 ? 4 : p % 2 == 0 ? 2 : 1, T = (hw / p) * (hw / p);
   const long threads = (long)hw / V * hw + (long)T * (ldo - 3 * p * p);      // of a plane, fills included
-  const int bpp = (int)((threads + 255) / 256);
-  const dim3 grid((unsigned)(3L * n_images * bpp));
-  if (V == 4) hipLaunchKernelGGL(im2col_kernel<4>, grid, dim3(256), 0, s, pix, hw, p, bpp, out, ldo, out_type);
-  else if (V == 2) hipLaunchKernelGGL(im2col_kernel<2>, grid, dim3(256), 0, s, pix, hw, p, bpp, out, ldo, out_type);
-  else hipLaunchKernelGGL(im2col_kernel<1>, grid, dim3(256), 0, s, pix, hw, p, bpp, out, ldo, out_type);
+  // (a launch holds 2^32 threads and 2^16 rows of blocks at most)
+  constexpr int PER = 65535 / 3;
+  const size_t es = out_type == ET_BF16 ? 2 : 4;
+  for (int i = 0; i < n_images; i += PER) {
+    const dim3 grid((unsigned)((threads + 255) / 256), 3 * std::min(PER, n_images - i));
+    const float* src = pix + 3L * i * hw * hw;
+    void* dst = static_cast<char*>(out) + (size_t)i * T * ldo * es;
+    if (V == 4) hipLaunchKernelGGL(im2col_kernel<4>, grid, dim3(256), 0, s, src, hw, p, dst, ldo, out_type);
+    else if (V == 2) hipLaunchKernelGGL(im2col_kernel<2>, grid, dim3(256), 0, s, src, hw, p, dst, ldo, out_type);
+    else hipLaunchKernelGGL(im2col_kernel<1>, grid, dim3(256), 0, s, src, hw, p, dst, ldo, out_type);
+  }
 }
 
 void launch_embed(const int32_t* ids, int B, int n, int vocab, const void* table, int table_type, int d, float* h,

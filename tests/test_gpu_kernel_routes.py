@@ -238,3 +238,54 @@ def test_f32_plans_name_what_is_launched(kw, stages):
         assert p["tile_n"] in (16, 32, 64) and p["tile_m"] in (16, 32, 64) and p["kg"] in (1, 4, 8), where
     assert m.replay_gemm(3, cfg.max_batch, 0)[1]["stages"] == stages          # the down projection: K = act_mlp
     m.close()
+
+
+# patch extraction of very many images: more rows of blocks than a launch
+# holds, and (17 GB of pixels, one a thread) more threads than fit one dimension
+@pytest.mark.parametrize("batch,hw,patch", [(4000, 8, 8), (4000, 245, 49)])
+def test_very_many_images(batch, hw, patch):
+    import torch
+    from paper_2609_12075_amd import synth, vla
+    cfg = synth.CONFIGS["tiny"].with_(name=f"tiny-many-{hw}", n_img=6, img_hw=hw, patch=patch, n_text=2, llm_d=64, n_q=1, n_kv=1,
+                                      llm_mlp=64, act_d=64, act_mlp=64, max_batch=batch)
+    if torch.cuda.mem_get_info()[0] < 8 * batch * 6 * 3 * hw * hw + (8 << 30):
+        pytest.skip("the card has not enough free memory for the pixels and their patches")
+    log(f"[images] {6 * batch} of {hw} x {hw}, patches of {patch}")
+    g = torch.Generator(device="cuda").manual_seed(7)
+    pix = torch.rand(batch, 6, 3, hw, hw, generator=g, device="cuda")
+    text = torch.randint(0, cfg.vocab, (batch, 2), generator=g, device="cuda", dtype=torch.int32)
+    w = synth.make_weights(cfg)
+    m = vla.Model(cfg, w)
+    kv = m.alloc_kv(batch)
+    m.prefill(batch, pix, text, kv)
+    torch.cuda.synchronize()
+    got = kv.view(torch.float32).view(cfg.llm_layers, 2, batch, 1, cfg.prefix_len, cfg.head_dim)
+    P = O.params(cfg, w)
+    for b in (0, batch // 2, batch - 1):
+        ref = O.prefill_row(cfg, P, pix[b].cpu().numpy(), text[b].cpu().numpy(), None)
+        for l in range(cfg.llm_layers):
+            for i, what in enumerate("kv"):
+                r, x = ref[what][l], got[l, i, b].cpu().numpy()
+                assert np.linalg.norm(x - r) <= 1e-4 * np.linalg.norm(r), (b, l, what)
+    m.close()
+
+
+@pytest.mark.parametrize("patch,bf16", [(8, False), (8, True), (6, True), (5, False)])
+def test_pixels_at_any_float(patch, bf16):
+    """Pixels one float past an aligned address give the same bits."""
+    import torch
+    from paper_2609_12075_amd import synth, vla
+    cfg = synth.CONFIGS["tiny"].with_(name=f"tiny-px{patch}-{bf16}", patch=patch, img_hw=3 * patch, action_dim=8,
+                                      dtype=synth.DTYPE_BF16 if bf16 else synth.DTYPE_F32)
+    m = vla.Model(cfg, synth.make_weights(cfg))
+    inp = synth.make_inputs(cfg, 3)
+    text, pix = torch.from_numpy(inp["text_ids"]).cuda(), torch.from_numpy(inp["pixels"]).cuda()
+    flat = torch.zeros(pix.numel() + 4, device="cuda")
+    flat[1:1 + pix.numel()] = pix.flatten()
+    kvs = []
+    for p in (pix, flat[1:1 + pix.numel()].view(pix.shape)):
+        kvs.append(m.alloc_kv(3))
+        m.prefill(3, p, text, kvs[-1])
+    torch.cuda.synchronize()
+    assert torch.equal(kvs[0], kvs[1])
+    m.close()
