@@ -9,7 +9,8 @@
 `traffic` scales the per-dispatch FETCH_SIZE / WRITE_SIZE counters (KiB) of
 the named kernel by what the same counters read for the 256 MiB device copy
 that `bench.py --copy-probe` runs (rocclr's copyBuffer kernel), and records
-the hash of the GEMM source so the figure is dropped once the kernel changes.
+the hash of the projection kernels' sources (and of the compiler's flags) so
+that the figure is dropped once they change.
 """
 from __future__ import annotations
 
@@ -24,11 +25,32 @@ import statistics
 import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
-GEMM_SOURCE = os.path.join(PKG, "csrc", "k_gemm.hip")
+CSRC = os.path.join(PKG, "csrc")
 
 
-def source_hash(path: str = GEMM_SOURCE) -> str:
-    return hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
+def projection_sources(csrc: str = CSRC) -> list:
+    """The files that the projection kernels are built from: every k_gemm*.hip
+    and, from there on, each file that one of them includes by name."""
+    todo = sorted(f for f in os.listdir(csrc) if f.startswith("k_gemm") and f.endswith(".hip"))
+    seen = []
+    while todo:
+        f = todo.pop(0)
+        if f in seen:
+            continue
+        seen.append(f)
+        with open(os.path.join(csrc, f)) as src:
+            todo += [g for g in re.findall(r'^\s*#include\s+"([^"]+)"', src.read(), re.M)
+                     if os.path.exists(os.path.join(csrc, g))]
+    return sorted(seen)
+
+
+def source_hash(csrc: str = CSRC) -> str:
+    from . import build
+    h = hashlib.sha256(" ".join(f for f in build.FLAGS if not f.startswith("/")).encode())
+    for f in projection_sources(csrc):
+        with open(os.path.join(csrc, f), "rb") as src:
+            h.update(f.encode() + b"\0" + src.read())
+    return h.hexdigest()[:16]
 
 
 def stats(path: str, top: int = 20) -> str:
