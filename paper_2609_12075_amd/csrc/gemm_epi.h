@@ -204,7 +204,6 @@ struct EpiRows {
       for (int it = 0; it < NIT; ++it) {
         aux[it] = (a.tab && ok[it]) ? *reinterpret_cast<const f32x4*>(a.tab + (long)(ms[it] % a.tab_period) * a.ldtab + n0)
                                     : zero;
-        off[it] = out_row(a, ms[it]) + n0;
       }
     } else if constexpr (MODE == EPI_RESID || MODE == EPI_EULER) {
       const float* out = reinterpret_cast<const float*>(a.out);
@@ -251,10 +250,11 @@ struct EpiRows {
 #pragma unroll
           for (int j = 0; j < 4; ++j) x[j] = act_apply(x[j], a.act);
         }
+        const long o = out_row(a, ms[it]) + n0;
         if (a.out_type == ET_BF16) {
-          *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(a.out) + off[it]) = bf16x4{(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
+          *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(a.out) + o) = bf16x4{(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
         } else {
-          *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.out) + off[it]) = x;
+          *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.out) + o) = x;
           if (a.out2)
             *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(a.out2) + (long)ms[it] * a.ldo2 + n0) =
                 bf16x4{(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
