@@ -422,10 +422,8 @@ __global__ void __launch_bounds__(512) attn_f32_kernel(AttnArgs a) {
     }
   }
   // merge the waves, the upper half into the lower until wave 0 holds all (a
-  // wave without keys has max -inf and sum 0, and weighs nothing; where no wave
-  // of the upper half has any, there is nothing to merge)
+  // wave without keys has max -inf and sum 0, and weighs nothing)
   for (int n = NW / 2; n > 0; n /= 2) {
-    if (n >= nt) continue;
     if (wave >= n && wave < 2 * n) {
       float* dst = mg[wave - n] + lane * REC;
 #pragma unroll
