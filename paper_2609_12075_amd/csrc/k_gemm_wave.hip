@@ -11,6 +11,7 @@
 // launch: with one output tile per CU such a product is bound by one or two
 // memory round trips plus the launch, not by the matrix pipe.
 #include <algorithm>
+#include <type_traits>
 
 #include "gemm_epi.h"
 #include "gemm_kernels.h"
@@ -313,13 +314,16 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   for (int i = 0; i < TN; ++i) wrow[i] = reinterpret_cast<const T*>(a.W) + (long)min(n0 + i * 16 + lr, a.N - 1) * a.ldw;
 #pragma unroll
   for (int j = 0; j < TM; ++j) arow[j] = reinterpret_cast<const T*>(a.A) + (long)min(m0 + j * 16 + lr, a.M - 1) * a.lda;
-  // the lane's E elements from k on, zeros past K (whole: none is)
+  // the lane's E elements from k on, zeros past K: all of them inside (WHOLE),
+  // all or none (VECTOR; bf16 always), or one by one
+  enum Piece { WHOLE, VECTOR, SINGLE };
   struct __attribute__((packed, aligned(sizeof(T)))) P { u32x4 v; };
-  auto frag = [&](const T* row, int k, bool whole) {
-    if constexpr (sizeof(T) == 2) {
+  auto frag = [&](const T* row, int k, auto how) {
+    if constexpr (how() == WHOLE) {
+      return reinterpret_cast<const P*>(row + k)->v;
+    } else if constexpr (how() == VECTOR) {
       return k < K ? reinterpret_cast<const P*>(row + k)->v : u32x4{0, 0, 0, 0};
     } else {
-      if (whole || k + 4 <= K) return reinterpret_cast<const P*>(row + k)->v;
       f32x4 v;
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = k + e < K ? (float)row[k + e] : 0.f;
@@ -337,18 +341,21 @@ __global__ void __launch_bounds__(64 * NW) gemm_gather_kernel(GemmArgs a) {
   const int nch = (K + CK - 1) / CK;
   for (int c0 = wave; c0 < nch; c0 += NW * U) {
     u32x4 wf[U][TN], af[U][TM];
-    auto load = [&](bool whole) {
+    auto load = [&](auto how) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int k = (c0 + u * NW) * CK + lk;
 #pragma unroll
-        for (int i = 0; i < TN; ++i) wf[u][i] = frag(wrow[i], k, whole);
+        for (int i = 0; i < TN; ++i) wf[u][i] = frag(wrow[i], k, how);
 #pragma unroll
-        for (int j = 0; j < TM; ++j) af[u][j] = frag(arow[j], k, whole);
+        for (int j = 0; j < TM; ++j) af[u][j] = frag(arow[j], k, how);
       }
     };
-    if (sizeof(T) == 4 && (c0 + (U - 1) * NW + 1) * CK <= K) load(true);
-    else load(false);
+    // (decided for the wave, so that a short K runs through little code)
+    if constexpr (sizeof(T) == 2) load(std::integral_constant<int, VECTOR>{});
+    else if ((c0 + (U - 1) * NW + 1) * CK <= K) load(std::integral_constant<int, WHOLE>{});
+    else if (K % 4 == 0) load(std::integral_constant<int, VECTOR>{});
+    else load(std::integral_constant<int, SINGLE>{});
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if constexpr (RMS) {
