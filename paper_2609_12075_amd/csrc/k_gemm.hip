@@ -629,7 +629,9 @@ static GemmPlan plan_base(const GemmArgs& a) {
     // (measured 10-15 % faster than 128 x 64 tiles with K-steps of 64 there).
     // kOneRoundCUs is below the chip's 256 because the action stage shares
     // the GPU with a VLM stage that holds some CUs' LDS: one-block-per-CU
-    // launches sized for all 256 CUs ran a second round there.
+    // launches sized for all 256 CUs ran a second round there (of these 96-135
+    // KiB blocks; the smaller ones of wave_plan are planned for 256, which
+    // measured the same there).
     // Up to 36 K-steps (K <= 4608), but past 32 only with K ranges: the ViT
     // MLP down (K = 4304) with two ranges at 256-768 rows is faster than on
     // the staged tiles (GR00T-like prefill at batch 1 3.765 -> 3.703 ms, the

@@ -495,7 +495,17 @@ WavePlan wave_plan(const GemmArgs& a) {
   // The smallest tile whose blocks leave no CU a second one. Up to 2 KiB of K
   // per row a 32 x 32 tile takes one ring slot (32 KiB of LDS, so that blocks
   // share CUs) and serves up to 640 blocks. Beyond, the staged tiles that
-  // share each operand row among more of a block's waves are faster. Measured
+  // share each operand row among more of a block's waves are faster: time over
+  // theirs by blocks, K 720 to 1024, stores, GeGLU and folded norms: to 550
+  // 0.74-0.85, to 640 0.92-1.04, to 750 0.93-1.05, to 900 1.07-1.12, over 1200
+  // 1.13-1.22. 64 x 64 tiles at such K: 0.98-1.11 of the staged ones' time.
+  // (A residual product with a row norm behind it is the exception, since its
+  // alternative is K ranges and their reduce: 960 x 960 x 960 with the norm
+  // 13.7 us there, 12.4 on 32 x 32 and 11.7 on 64 x 64 tiles.) 256 CUs, though
+  // the action stage may share them with a VLM stage: planned for 192, a
+  // lockstep of the pi0-shaped VLM stage and the SmolVLA-shaped action stage
+  // takes as long (2641 and 2645 us), for 128 or 64 longer (2690, 2697).
+  // Measured
   // (us, this kernel against the plans used before it, replayed graph): 50
   // rows, 1600 x 720 3.7 / 6.1, 720 x 960 3.3 / 6.0, 3840 x 720 4.1 / 5.6,
   // 720 x 1920 3.8 / 6.6, 2560 x 1024 4.5 / 7.3, 8192 x 1024 6.1 / 9.3,
